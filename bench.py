@@ -711,7 +711,7 @@ def prelude_main(args):
         "roofline": {
             "bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
             "frac": round(achieved / PEAK_HBM_GBS, 4), "traffic": traffic,
-            "kernel": "gemv_kernel (packed-weight MFMA GEMV of the QKV projection)",
+            "kernel": "rows_kernel (packed-weight MFMA GEMV of the QKV projection)",
             "frac_of_stream_read": round(achieved / stream_ref["gbs"], 4),
             "frac_of_same_size_stream_read": round(achieved / same["gbs"], 4),
         },
@@ -818,7 +818,7 @@ def oproj_main(args):
         "graph_us_per_call": None if graph_us is None else round(graph_us, 2),
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                      "frac": round(achieved / PEAK_HBM_GBS, 4), "traffic": _gemv_traffic(args.workload),
-                     "kernel": "gemv_kernel (packed-weight MFMA GEMV of the output projection)",
+                     "kernel": "rows_kernel (packed-weight MFMA GEMV of the output projection)",
                      "frac_of_stream_read": round(achieved / stream_ref["gbs"], 4),
                      "frac_of_same_size_stream_read": round(achieved / same["gbs"], 4)},
         "stream_read": stream_ref,

@@ -654,23 +654,35 @@ int64_t prelude_rows(const pda_prelude_dims& d) {
   return static_cast<int64_t>(d.num_q_heads + 2 * d.num_kv_heads) * d.head_dim;
 }
 
-// The GEMV plan of a prelude on this device's compute units.
-pda::GemvPlan prelude_plan(const pda_prelude_dims& d, int cus) {
-  return pda::plan_gemv(d.batch, static_cast<int>(prelude_rows(d)), d.hidden, cus);
+bool overlaps(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + static_cast<uintptr_t>(b_bytes) && y < x + static_cast<uintptr_t>(a_bytes);
 }
 
+// Workspace of a prelude whose epilogue is a kernel of its own: the fp32
+// projection, one per k split.  (Reserved for every prelude: the reservation
+// does not know the norm weights.)
 int64_t prelude_ws_bytes(const pda_prelude_dims& d, int cus) {
-  return align256(pda::gemv_partial_floats(prelude_plan(d, cus), d.batch, static_cast<int>(prelude_rows(d))) * 4);
+  const pda::RowsPlan plan =
+      pda::plan_rows(d.batch, static_cast<int>(prelude_rows(d)), d.hidden, cus, false, pda::kMaxRowsSplits);
+  return align256(static_cast<int64_t>(plan.splits) * d.batch * prelude_rows(d) * 4);
 }
 
-// o_proj workspace: GEMV partials, then z [batch, hidden] and the chunk sums.
-int64_t oproj_z_offset(const pda::GemvPlan& plan, int batch, int hidden) {
-  return align256(pda::gemv_partial_floats(plan, batch, hidden) * 4);
+// k splits only where the kernel that adds them holds a row of z.
+pda::RowsPlan oproj_plan(int batch, int in_features, int hidden, int cus) {
+  return pda::plan_rows(batch, hidden, in_features, cus, false,
+                        hidden <= pda::kSumFeatures ? pda::kMaxRowsSplits : 1);
 }
 
-int64_t oproj_ws_bytes(const pda::GemvPlan& plan, int batch, int hidden) {
-  return oproj_z_offset(plan, batch, hidden) +
-         align256((static_cast<int64_t>(batch) * hidden + static_cast<int64_t>(batch) * pda::oproj_chunks(hidden)) * 4);
+// o_proj workspace: z [splits, batch, hidden] in fp32, then the partial sums
+// of z^2.
+int64_t oproj_ss_offset(const pda::RowsPlan& plan, int batch, int hidden) {
+  return align256(static_cast<int64_t>(plan.splits) * batch * hidden * 4);
+}
+
+int64_t oproj_ws_bytes(const pda::RowsPlan& plan, int batch, int hidden) {
+  return oproj_ss_offset(plan, batch, hidden) +
+         align256(static_cast<int64_t>(batch) * (hidden / pda::kTileRows) * plan.ss_parts * 4);
 }
 
 // Shared by both prelude entry points once their own arguments are checked.
@@ -691,23 +703,14 @@ int run_prelude(const void* x, const void* w_packed, const void* bias, const voi
   int rc = device_cus(dev, &cus);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  void* ws = nullptr;
-  if ((rc = workspace_for(dev, st, prelude_ws_bytes(d, cus), &ws))) return rc;
-  pda::GemvArgs g;
+  pda::RowsArgs g;
   g.x = static_cast<const uint16_t*>(x);
   g.wp = static_cast<const uint16_t*>(w_packed);
-  g.part = static_cast<float*>(ws);
+  g.y = nullptr;
   g.batch = d.batch;
   g.n = static_cast<int>(prelude_rows(d));
   g.k = d.hidden;
-  g.plan = prelude_plan(d, cus);
-  const Rec rec = prof_begin(1);
-  const bool prof = rec.a != nullptr;
-  if (prof && (e = hipEventRecord(rec.a, st)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-  if ((e = pda::launch_gemv(g, st)) != hipSuccess) return hip_fail(e, "GEMV kernel launch");
-  if (prof && (e = hipEventRecord(rec.b, st)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-  ep.part = g.part;
-  ep.plan = g.plan;
+  ep.y = nullptr;
   ep.bias = static_cast<const uint16_t*>(bias);
   ep.q_norm = static_cast<const uint16_t*>(q_norm);
   ep.k_norm = static_cast<const uint16_t*>(k_norm);
@@ -725,7 +728,38 @@ int run_prelude(const void* x, const void* w_packed, const void* bias, const voi
       ep.freq_pow2[k] = d.rotary_dim > 0 ? std::exp2(-(2.0 * (1 << k) / d.rotary_dim) * log2_theta) : 0.0;
   }
   ep.eps = d.eps;
-  if ((e = pda::launch_prelude_epilogue(ep, st)) != hipSuccess) return hip_fail(e, "prelude epilogue launch");
+  // The epilogue runs in the projection kernel where it can, unless an
+  // output lies over something that kernel still reads for other outputs:
+  // then the projection goes through the workspace.
+  bool fusable = pda::prelude_fusable(ep);
+  if (fusable) {
+    const int64_t kv_bytes = static_cast<int64_t>(d.batch) * d.num_kv_heads * d.head_dim * 2;
+    const int64_t cache_bytes =
+        ep.k_cache ? (static_cast<int64_t>(ep.num_pages) << ep.page_shift) * d.num_kv_heads * d.head_dim * 2 : 0;
+    const struct { const void* p; int64_t bytes; } outs[] = {
+        {q_out, static_cast<int64_t>(d.batch) * d.num_q_heads * d.head_dim * 2},
+        {ep.k_out, kv_bytes}, {ep.v_out, kv_bytes}, {ep.k_cache, cache_bytes}, {ep.v_cache, cache_bytes}};
+    for (const auto& o : outs)
+      fusable = fusable && !overlaps(o.p, o.bytes, x, static_cast<int64_t>(d.batch) * d.hidden * 2) &&
+              !overlaps(o.p, o.bytes, w_packed, static_cast<int64_t>(g.n) * g.k * 2);
+  }
+  const pda::RowsPlan plan = pda::plan_rows(g.batch, g.n, g.k, cus, fusable, pda::kMaxRowsSplits);
+  const bool fused = plan.fused;
+  if (!fused) {
+    void* ws = nullptr;
+    if ((rc = workspace_for(dev, st, prelude_ws_bytes(d, cus), &ws))) return rc;
+    g.y = static_cast<float*>(ws);
+    ep.y = g.y;
+    ep.splits = plan.splits;
+  }
+  const Rec rec = prof_begin(1);
+  const bool prof = rec.a != nullptr;
+  if (prof && (e = hipEventRecord(rec.a, st)) != hipSuccess) return hip_fail(e, "hipEventRecord");
+  e = fused ? pda::launch_rows_prelude(g, plan, ep, st) : pda::launch_rows(g, plan, st);
+  if (e != hipSuccess) return hip_fail(e, "GEMV kernel launch");
+  if (prof && (e = hipEventRecord(rec.b, st)) != hipSuccess) return hip_fail(e, "hipEventRecord");
+  if (!fused && (e = pda::launch_prelude_epilogue(ep, st)) != hipSuccess)
+    return hip_fail(e, "prelude epilogue launch");
   if (prof) {
     if ((e = hipEventRecord(rec.c, st)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     prof_push(rec);
@@ -1230,35 +1264,36 @@ int pda_o_proj_residual_norm(const void* attn, const void* w_packed, const void*
   int rc = device_cus(dev, &cus);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const pda::GemvPlan plan = pda::plan_gemv(batch, hidden, in_features, cus, /*seq_major=*/true);
+  const pda::RowsPlan plan = oproj_plan(batch, in_features, hidden, cus);
   void* ws = nullptr;
   if ((rc = workspace_for(dev, st, oproj_ws_bytes(plan, batch, hidden), &ws))) return rc;
-  pda::GemvArgs g;
-  g.x = static_cast<const uint16_t*>(attn);
-  g.wp = static_cast<const uint16_t*>(w_packed);
-  g.part = static_cast<float*>(ws);
-  g.batch = batch;
-  g.n = hidden;
-  g.k = in_features;
-  g.plan = plan;
-  const Rec rec = prof_begin(2);
-  const bool prof = rec.a != nullptr;
-  if (prof && (e = hipEventRecord(rec.a, st)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-  if ((e = pda::launch_gemv(g, st)) != hipSuccess) return hip_fail(e, "GEMV kernel launch");
-  if (prof && (e = hipEventRecord(rec.b, st)) != hipSuccess) return hip_fail(e, "hipEventRecord");
   pda::OProjArgs o;
-  o.part = g.part;
-  o.plan = plan;
   o.residual = static_cast<const uint16_t*>(residual);
   o.norm_w = static_cast<const uint16_t*>(norm_w);
   o.residual_out = static_cast<uint16_t*>(residual_out);
   o.normed_out = static_cast<uint16_t*>(normed_out);
-  o.z = reinterpret_cast<float*>(static_cast<char*>(ws) + oproj_z_offset(plan, batch, hidden));
-  o.chunk_ss = o.z + static_cast<int64_t>(batch) * hidden;
+  o.z = static_cast<float*>(ws);
+  o.splits = plan.splits;
+  o.ss = reinterpret_cast<float*>(static_cast<char*>(ws) + oproj_ss_offset(plan, batch, hidden));
+  o.ss_count = hidden / pda::kTileRows * plan.ss_parts;
   o.batch = batch;
   o.hidden = hidden;
   o.eps = eps;
-  if ((e = pda::launch_oproj_epilogue(o, st)) != hipSuccess) return hip_fail(e, "o_proj epilogue launch");
+  pda::RowsArgs g;
+  g.x = static_cast<const uint16_t*>(attn);
+  g.wp = static_cast<const uint16_t*>(w_packed);
+  g.y = o.z;
+  g.batch = batch;
+  g.n = hidden;
+  g.k = in_features;
+  const Rec rec = prof_begin(2);
+  const bool prof = rec.a != nullptr;
+  if (prof && (e = hipEventRecord(rec.a, st)) != hipSuccess) return hip_fail(e, "hipEventRecord");
+  e = plan.splits > 1 ? pda::launch_rows(g, plan, st) : pda::launch_rows_residual(g, plan, o, st);
+  if (e != hipSuccess) return hip_fail(e, "GEMV kernel launch");
+  if (prof && (e = hipEventRecord(rec.b, st)) != hipSuccess) return hip_fail(e, "hipEventRecord");
+  e = plan.splits > 1 ? pda::launch_oproj_sum(o, st) : pda::launch_oproj_norm(o, st);
+  if (e != hipSuccess) return hip_fail(e, "o_proj norm launch");
   if (prof) {
     if ((e = hipEventRecord(rec.c, st)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     prof_push(rec);
@@ -1279,7 +1314,7 @@ int pda_o_proj_workspace_reserve(int32_t batch, int32_t in_features, int32_t hid
   int cus = 0;
   int rc = device_cus(dev, &cus);
   if (rc) return rc;
-  const pda::GemvPlan plan = pda::plan_gemv(batch, hidden, in_features, cus, /*seq_major=*/true);
+  const pda::RowsPlan plan = oproj_plan(batch, in_features, hidden, cus);
   void* ptr = nullptr;
   return workspace_for(dev, static_cast<hipStream_t>(stream), oproj_ws_bytes(plan, batch, hidden), &ptr);
 }

@@ -14,35 +14,31 @@
 //    8 (l / 16) .. +7 of it.  Every weight load of the GEMV is then one
 //    contiguous 1 KB wave access that feeds v_mfma_f32_16x16x32_bf16
 //    directly, with no LDS staging and no lane shuffles.
-//  * The batch forms the MFMA's B columns in 16-column tiles (up to four in
-//    gemv_kernel, up to sixteen -- 256 sequences -- in the thin-GEMM form);
-//    x rows past the batch read as zeros through the buffer descriptor's
-//    size.
-//  * Stream-K over (row group, 32-k tile) units: every workgroup of a grid
-//    sized to the device streams the same number of packed weight tiles,
-//    whatever the shape, so no half-empty last round of workgroups.  The
-//    waves of a workgroup split its k tiles and add their accumulators in
-//    LDS; the workgroup leaves one fp32 partial per row group it touched and
-//    the epilogue adds a group's partials in workgroup order.
-//  * The epilogue (partial sums, bias, RMSNorm, rotation, bf16 rounding, and
-//    optionally the KV append into the page slot) runs per (sequence, head):
-//    a head's norm and its rotation pairs need all of its rows, which no
-//    single wave of the GEMV holds.
+//  * The batch forms the MFMA's B columns in tiles of 16 sequences; x rows
+//    past the batch read as zeros through the buffer descriptor's size.
+//  * A workgroup computes its output rows over the whole k range (or one of
+//    a few splits), see rows_kernel, so most preludes end in the same kernel:
+//    bias, rotation, bf16 rounding and the KV append into the page slot.
+//    With a per-head RMSNorm, which needs all rows of a head, and in a few
+//    large shapes the epilogue is a kernel of its own.
 //
 // The output projection after attention (kernel family (v): o_proj GEMV +
-// residual add + the RMSNorm that follows) runs on the same GEMV; its
-// epilogue works in two passes over (sequence, chunk of features), since the
-// norm spans all hidden features of a sequence.
+// residual add + the RMSNorm that follows) runs on the same kernel, which
+// adds the residual and leaves z in fp32 with partial sums of z^2; the norm
+// spans all features of a sequence and is a second, small kernel.
 #include "pda_gemv.h"
 
 #include <atomic>
-#include <cstdlib>
+#include <cmath>
+#include <type_traits>
+#include <utility>
 
 namespace pda {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBufferDword3 = 0x00020000;  // raw 32-bit buffer format
@@ -77,542 +73,6 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(const uint16_t* __re
   *reinterpret_cast<u32x4*>(wp + chunk * 8) = *reinterpret_cast<const u32x4*>(w + row * k + col);
 }
 
-// Stream-K GEMV: the flattened space of (row group g, 32-k tile) units is
-// cut into equal contiguous ranges, one per workgroup, so every workgroup
-// streams the same number of packed weight tiles whatever the matrix shape.
-// A row group is kR consecutive 16-row tiles: each x fragment a wave loads
-// feeds kR MFMAs, which keeps x reads (L2) at or below the weight reads
-// (HBM) when the batch spans several 16-column tiles, and cuts them 4x
-// within one tile of more than 4 sequences.  Inside a workgroup
-// the 4 waves split each group segment's k tiles into contiguous quarters
-// and add their accumulators in LDS; the workgroup then writes one partial
-// (kR tiles x batch, fp32) per row group its range touches, into slot
-// j = workgroup - first_workgroup(g) of that group, and the epilogue sums a
-// group's slots in order (deterministic).
-template <int kNBT, int kR>
-__global__ __launch_bounds__(kGemvThreads, gemv_min_waves_per_simd(kNBT, kR)) void gemv_kernel(
-    const uint16_t* __restrict__ x, const uint16_t* __restrict__ wp, float* __restrict__ part, int batch, int n,
-    int k, int slots, int seq_major) {
-  __shared__ f32x4 red[kGemvWaves][kR * kNBT][64];
-  const int lane = threadIdx.x & 63;
-  const int wv = uniform(threadIdx.x >> 6);
-  const int64_t blocks = gridDim.x;
-  const int64_t blk = blockIdx.x;
-  const int kt_count = k / kTileK;
-  const int64_t units = static_cast<int64_t>(n / (kTileRows * kR)) * kt_count;
-  int64_t u = blk * units / blocks;
-  const int64_t u_end = (blk + 1) * units / blocks;
-
-  // x rows at or past the batch fall outside the descriptor and read as zeros
-  const __amdgpu_buffer_rsrc_t rx = make_rsrc(x, static_cast<uint32_t>(batch) * k * 2u);
-  const int r = lane & 15;
-  const int g4 = lane >> 4;
-  int xrow[kNBT];
-#pragma unroll
-  for (int bt = 0; bt < kNBT; ++bt) xrow[bt] = ((16 * bt + r) * k + 8 * g4) * 2;
-
-  while (u < u_end) {
-    const int g = static_cast<int>(u / kt_count);
-    const int64_t seg_end = u_end < static_cast<int64_t>(g + 1) * kt_count ? u_end
-                                                                           : static_cast<int64_t>(g + 1) * kt_count;
-    const int seg = static_cast<int>(seg_end - u);
-    // this wave's quarter of the segment: k tiles [kt0, kt0 + per)
-    const int lo = wv * seg / kGemvWaves;
-    const int per = (wv + 1) * seg / kGemvWaves - lo;
-    const int kt0 = static_cast<int>(u - static_cast<int64_t>(g) * kt_count) + lo;
-    const uint16_t* wbase = wp + (static_cast<int64_t>(g) * kR * kt_count + kt0) * (kTileRows * kTileK);
-    __amdgpu_buffer_rsrc_t rw[kR];
-#pragma unroll
-    for (int i = 0; i < kR; ++i)  // k tiles past the quarter read as zeros (outside the descriptor)
-      rw[i] = make_rsrc(wbase + static_cast<int64_t>(i) * kt_count * (kTileRows * kTileK),
-                        static_cast<uint32_t>(per) * 1024u);
-
-    f32x4 acc[kR][kNBT];
-#pragma unroll
-    for (int i = 0; i < kR; ++i)
-#pragma unroll
-      for (int bt = 0; bt < kNBT; ++bt) acc[i][bt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // k tiles in chunks, the next chunk's loads in flight while the current
-    // chunk's MFMAs run
-    constexpr int kChunk = kNBT * kR >= 4 ? 2 : (kNBT == 1 ? 8 : 4);
-    u32x4 wa[2][kChunk][kR];
-    u32x4 xb[2][kChunk][kNBT];
-    auto load = [&](int buf, int j0) {
-#pragma unroll
-      for (int j = 0; j < kChunk; ++j) {
-#pragma unroll
-        for (int i = 0; i < kR; ++i)
-          wa[buf][j][i] = __builtin_amdgcn_raw_buffer_load_b128(rw[i], (j0 + j) * 1024 + 16 * lane, 0, kCachePolicyNT);
-        const bool in = j0 + j < per;
-#pragma unroll
-        for (int bt = 0; bt < kNBT; ++bt)
-          xb[buf][j][bt] = in ? __builtin_amdgcn_raw_buffer_load_b128(rx, xrow[bt] + (kt0 + j0 + j) * kTileK * 2, 0, 0)
-                              : u32x4{0u, 0u, 0u, 0u};
-      }
-    };
-    auto mma = [&](int buf) {
-#pragma unroll
-      for (int j = 0; j < kChunk; ++j)
-#pragma unroll
-        for (int i = 0; i < kR; ++i)
-#pragma unroll
-          for (int bt = 0; bt < kNBT; ++bt)
-            acc[i][bt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[buf][j][i]),
-                                                                 __builtin_bit_cast(bf16x8, xb[buf][j][bt]),
-                                                                 acc[i][bt], 0, 0, 0);
-    };
-    const int chunks = (per + kChunk - 1) / kChunk;
-    if (chunks > 0) {
-      load(0, 0);
-      int c = 0;
-      for (; c + 2 <= chunks; c += 2) {
-        load(1, (c + 1) * kChunk);
-        mma(0);
-        if (c + 2 < chunks) load(0, (c + 2) * kChunk);
-        mma(1);
-      }
-      if (c < chunks) mma(0);
-    }
-
-    // the 4 waves' accumulators meet in LDS; wave wv adds and stores the
-    // (tile, column tile) pairs wv, wv + 4, ...
-#pragma unroll
-    for (int i = 0; i < kR; ++i)
-#pragma unroll
-      for (int bt = 0; bt < kNBT; ++bt) red[wv][i * kNBT + bt][lane] = acc[i][bt];
-    __syncthreads();
-    // C layout: lane holds rows 4 (l / 16) + i, column l % 16 of its tile
-    const int64_t first = (static_cast<int64_t>(g) * kt_count * blocks + blocks - 1) / units;  // first block of g
-    float* slot = part + (static_cast<int64_t>(g) * slots + (blk - first)) * kR * batch * kTileRows;
-    for (int p = wv; p < kR * kNBT; p += kGemvWaves) {
-      const int i = p / kNBT;
-      const int bt = p - i * kNBT;
-      f32x4 sum = red[0][p][lane];
-#pragma unroll
-      for (int w2 = 1; w2 < kGemvWaves; ++w2) sum += red[w2][p][lane];
-      const int b = 16 * bt + r;
-      const int row = seq_major ? b * kR + i : i * batch + b;
-      if (b < batch) *reinterpret_cast<f32x4*>(slot + row * kTileRows + 4 * g4) = sum;
-    }
-    __syncthreads();  // red is rewritten by the next segment
-    u = seg_end;
-  }
-}
-
-// Thin-GEMM form of the same stream-K GEMV for batches of more than 16
-// sequences.  A workgroup of kXWaves waves works on row groups of kXWaves
-// row tiles, wave w on tile w of the group, over the group's k range in
-// chunks of kXChunk k tiles: the chunk's activations (batch x kXChunk x 32
-// bf16) are loaded once per workgroup with row-contiguous reads and staged
-// in LDS, where every wave reads its B fragments; the weights come straight
-// from the packed tiles into registers, kXDepth chunks ahead.  Compared with
-// gemv_kernel (x fragments loaded per wave, 16 rows x 64 bytes per load,
-// reused across the group's row tiles in registers), the x reads from L2
-// halve and are contiguous, and no cross-wave reduction is needed since each
-// wave owns its rows.  Partials and their layout are gemv_kernel's (group =
-// kXWaves tiles), so the epilogues are shared.
-template <int kNBT>
-__global__ __launch_bounds__(kXWaves * 64, 1) void gemv_xlds_kernel(
-    const uint16_t* __restrict__ x, const uint16_t* __restrict__ wp, float* __restrict__ part, int batch, int n,
-    int k, int slots, int seq_major) {
-  extern __shared__ __align__(16) unsigned char xs[];  // [kXRing][kNBT * 16 rows][kXRowBytes]
-  constexpr int kRows = kNBT * kTileRows;
-  constexpr int kBuf = kRows * kXRowBytes;
-  constexpr int kRowPieces = kXChunk * kTileK / 8;                       // 16-byte pieces per row and chunk
-  constexpr int kPieces = kRows * kRowPieces;
-  constexpr int kPer = (kPieces + kXWaves * 64 - 1) / (kXWaves * 64);  // per thread
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wv = uniform(tid >> 6);
-  const int64_t blocks = gridDim.x;
-  const int64_t blk = blockIdx.x;
-  const int kt_count = k / kTileK;
-  const int64_t units = static_cast<int64_t>(n / (kTileRows * kXWaves)) * kt_count;
-  int64_t u = blk * units / blocks;
-  const int64_t u_end = (blk + 1) * units / blocks;
-  // x rows at or past the batch fall outside the descriptor and read as zeros
-  const __amdgpu_buffer_rsrc_t rx = make_rsrc(x, static_cast<uint32_t>(batch) * k * 2u);
-  const int r = lane & 15;
-  const int g4 = lane >> 4;
-  constexpr uint32_t kOutside = 0x80000000u;  // a buffer offset past any descriptor: reads zero
-
-  while (u < u_end) {
-    const int g = static_cast<int>(u / kt_count);
-    const int64_t seg_end = u_end < static_cast<int64_t>(g + 1) * kt_count ? u_end
-                                                                           : static_cast<int64_t>(g + 1) * kt_count;
-    const int kt_a = static_cast<int>(u - static_cast<int64_t>(g) * kt_count);
-    const int seg = static_cast<int>(seg_end - u);
-    const int nch = (seg + kXChunk - 1) / kXChunk;
-    // this wave's row tile over the segment; k tiles past it read as zeros
-    const uint16_t* wbase = wp + ((static_cast<int64_t>(g) * kXWaves + wv) * kt_count + kt_a) * (kTileRows * kTileK);
-    const __amdgpu_buffer_rsrc_t rw = make_rsrc(wbase, static_cast<uint32_t>(seg) * 1024u);
-
-    f32x4 acc[kNBT];
-#pragma unroll
-    for (int bt = 0; bt < kNBT; ++bt) acc[bt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    u32x4 wa[kXRing][kXChunk];
-    u32x4 xr[kPer];
-    // chunks past the segment load nothing (zero-size reads), so every
-    // iteration issues the same loads and the waits are one count
-    auto load_w = [&](int buf, int c) {
-#pragma unroll
-      for (int j = 0; j < kXChunk; ++j)
-        wa[buf][j] = __builtin_amdgcn_raw_buffer_load_b128(rw, (c * kXChunk + j) * 1024 + 16 * lane, 0, kCachePolicyNT);
-    };
-    // piece q: row q / kRowPieces, 16 bytes at k 8 (q % kRowPieces) of the chunk
-    auto load_x = [&](int c) {
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        const int q = tid + i * kXWaves * 64;
-        const int row = q / kRowPieces;
-        const int kk = c * kXChunk * kTileK + 8 * (q % kRowPieces);  // k within the segment
-        const bool live = q < kPieces && kk < seg * kTileK;
-        const uint32_t off = live ? static_cast<uint32_t>((row * k + kt_a * kTileK + kk) * 2) : kOutside;
-        xr[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, off, 0, 0);
-      }
-    };
-    auto store_x = [&](int buf) {
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        const int q = tid + i * kXWaves * 64;
-        if (q < kPieces)
-          *reinterpret_cast<u32x4*>(xs + buf * kBuf + (q / kRowPieces) * kXRowBytes + 16 * (q % kRowPieces)) = xr[i];
-      }
-    };
-    auto mma = [&](int buf) {
-#pragma unroll
-      for (int j = 0; j < kXChunk; ++j) {
-#pragma unroll
-        for (int bt = 0; bt < kNBT; ++bt) {
-          const u32x4 b = *reinterpret_cast<const u32x4*>(xs + buf * kBuf + (16 * bt + r) * kXRowBytes + 64 * j + 16 * g4);
-          acc[bt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[buf][j]),
-                                                            __builtin_bit_cast(bf16x8, b), acc[bt], 0, 0, 0);
-        }
-      }
-    };
-    // x of chunk c + 1 and the weights of chunk c + kXDepth are in flight
-    // while chunk c computes; x goes through a ring of kXRing LDS buffers,
-    // so one barrier per chunk orders its writes after the last reads
-    load_x(0);
-#pragma unroll
-    for (int d = 0; d < kXDepth; ++d) load_w(d, d);
-    for (int c0 = 0; c0 < nch; c0 += kXRing) {
-#pragma unroll
-      for (int sl = 0; sl < kXRing; ++sl) {
-        const int c = c0 + sl;
-        if (c < nch) {
-          // everything but the weights issued after x of chunk c has arrived
-          __builtin_amdgcn_s_waitcnt(kWaitVmcntWeights);
-          store_x(sl);
-          load_x(c + 1);
-          load_w((sl + kXDepth) % kXRing, c + kXDepth);
-          __syncthreads();
-          mma(sl);
-        }
-      }
-    }
-    // this wave's rows of the group: one partial per (workgroup, group)
-    const int64_t first = (static_cast<int64_t>(g) * kt_count * blocks + blocks - 1) / units;  // first block of g
-    float* slot = part + (static_cast<int64_t>(g) * slots + (blk - first)) * kXWaves * batch * kTileRows;
-#pragma unroll
-    for (int bt = 0; bt < kNBT; ++bt) {
-      const int b = 16 * bt + r;
-      const int row = seq_major ? b * kXWaves + wv : wv * batch + b;
-      if (b < batch) *reinterpret_cast<f32x4*>(slot + row * kTileRows + 4 * g4) = acc[bt];
-    }
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // the loads issued past the segment
-    __syncthreads();                     // the LDS buffers are rewritten by the next segment
-    u = seg_end;
-  }
-}
-
-// Thin-GEMM form for the largest batches, with the activations copied
-// straight into LDS.  The B fragments of a chunk (kC k tiles x kNBT column
-// tiles, 1 KB each) are fetched by the workgroup's waves with buffer loads
-// that write LDS directly (no registers, no LDS store instructions): lane l
-// of such a load fetches x[16 bt + l % 16][32 kt + 8 (l / 16) .. +7], so each
-// fragment lands in LDS in exactly the order the matrix cores read it and
-// every LDS read of a fragment is one contiguous, conflict-free 1 KB wave
-// access.  Weights come from the packed tiles into registers, kR row tiles
-// per wave, so each B fragment read from LDS feeds kR MFMAs: at 256
-// sequences a wave of gemv_xlds_kernel reads 16 KB of fragments from LDS per
-// 1 KB weight tile, this form 8 KB.  Activations and weights are both kD
-// chunks ahead through a ring of kD + 1 stages, with one barrier per chunk.
-// The workgroup's range of (row group, k tile) units is walked as one
-// stream: where it passes into the next row group the accumulators are
-// written out as that group's partial and cleared, while the loads keep
-// flowing.  Partials and their layout are gemv_kernel's (group = kW kR row
-// tiles).
-template <int kNBT, int kW, int kR, int kC, int kD>
-__global__ __launch_bounds__(kW * 64, 1) void gemv_thin_kernel(const uint16_t* __restrict__ x,
-                                                               const uint16_t* __restrict__ wp,
-                                                               float* __restrict__ part, int batch, int n, int k,
-                                                               int slots) {
-  extern __shared__ __align__(1024) unsigned char xs[];  // [kD + 1][kC][kNBT] fragments of 1 KB
-  constexpr int kGroup = kW * kR;
-  constexpr int kFrags = kC * kNBT;
-  static_assert(kFrags % kW == 0, "every wave copies the same number of fragments");
-  constexpr int kDma = kFrags / kW;
-  constexpr int kStages = kD + 1;
-  constexpr int kLoads = kDma + kC * kR;  // vector memory instructions per wave and chunk
-  static_assert(kD >= 2, "the next chunk's loads are waited for while later ones stay in flight");
-  constexpr int kAheadFirst = (kD - 1) * kLoads;  // after chunk 0's loads
-  constexpr int kAheadNext = (kD - 2) * kLoads;   // after chunk c + 1's loads, at chunk c
-  static_assert(kAheadFirst < 64, "vmcnt holds at most 63");
-  // vmcnt(n) with expcnt and lgkmcnt not waited for / with lgkmcnt(0)
-  constexpr int kWaitFirst = 0x0F70 | (kAheadFirst & 15) | ((kAheadFirst >> 4) << 14);
-  constexpr int kWaitNext = 0x0070 | (kAheadNext & 15) | ((kAheadNext >> 4) << 14);
-  constexpr uint32_t kOutside = 0x80000000u;  // past any descriptor of x: reads zero
-  const int lane = threadIdx.x & 63;
-  const int wv = uniform(threadIdx.x >> 6);
-  const int64_t blocks = gridDim.x;
-  const int64_t blk = blockIdx.x;
-  const int kt_count = k / kTileK;
-  const int64_t units = static_cast<int64_t>(n / (kTileRows * kGroup)) * kt_count;
-  const int64_t u0 = blk * units / blocks;
-  const int64_t u1 = (blk + 1) * units / blocks;
-  const int nch = static_cast<int>((u1 - u0 + kC - 1) / kC);
-  // x rows at or past the batch fall outside the descriptor and read as zeros
-  const __amdgpu_buffer_rsrc_t rx = make_rsrc(x, static_cast<uint32_t>(batch) * k * 2u);
-  const uint32_t xlane = static_cast<uint32_t>(((lane & 15) * k + 8 * (lane >> 4)) * 2);
-
-  // load stream: the (group, k tile) of the next unit to fetch
-  int lg = static_cast<int>(u0 / kt_count);
-  int lkt = static_cast<int>(u0 - static_cast<int64_t>(lg) * kt_count);
-  int64_t lu = u0;
-  u32x4 wa[kStages][kC][kR];
-  auto issue = [&](int stage) __attribute__((always_inline)) {
-    int gj[kC], ktj[kC];
-    bool live[kC];
-#pragma unroll
-    for (int j = 0; j < kC; ++j) {
-      gj[j] = lg;
-      ktj[j] = lkt;
-      live[j] = lu < u1;
-      ++lu;
-      if (++lkt == kt_count) {
-        lkt = 0;
-        ++lg;
-      }
-    }
-#pragma unroll
-    for (int d = 0; d < kDma; ++d) {
-      const int f = wv * kDma + d;  // fragment (j, bt) of the chunk
-      const int j = f / kNBT;
-      const int bt = f - j * kNBT;
-      const uint32_t off = live[j] ? xlane + static_cast<uint32_t>((16 * bt * k + ktj[j] * kTileK) * 2) : kOutside;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(xs + (stage * kFrags + f) * 1024),
-                                               16, off, 0, 0, 0);
-    }
-#pragma unroll
-    for (int j = 0; j < kC; ++j) {
-#pragma unroll
-      for (int r = 0; r < kR; ++r) {
-        const int64_t tile = static_cast<int64_t>(gj[j]) * kGroup + wv * kR + r;
-        const __amdgpu_buffer_rsrc_t rw =
-            make_rsrc(wp + (tile * kt_count + ktj[j]) * (kTileRows * kTileK), live[j] ? 1024u : 0u);
-        wa[stage][j][r] = __builtin_amdgcn_raw_buffer_load_b128(rw, 16 * lane, 0, kCachePolicyNT);
-      }
-    }
-  };
-
-  f32x4 acc[kR][kNBT];
-#pragma unroll
-  for (int r = 0; r < kR; ++r)
-#pragma unroll
-    for (int bt = 0; bt < kNBT; ++bt) acc[r][bt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int r16 = lane & 15;
-  const int g4 = lane >> 4;
-  // this wave's rows of group g as the workgroup's partial of g, then cleared
-  auto flush = [&](int g) __attribute__((always_inline)) {
-    const int64_t first = (static_cast<int64_t>(g) * kt_count * blocks + blocks - 1) / units;  // first block of g
-    float* slot = part + (static_cast<int64_t>(g) * slots + (blk - first)) * kGroup * batch * kTileRows;
-#pragma unroll
-    for (int r = 0; r < kR; ++r)
-#pragma unroll
-      for (int bt = 0; bt < kNBT; ++bt) {
-        const int b = 16 * bt + r16;
-        if (b < batch) *reinterpret_cast<f32x4*>(slot + ((wv * kR + r) * batch + b) * kTileRows + 4 * g4) = acc[r][bt];
-        acc[r][bt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
-  };
-  // compute stream: the (group, k tile) of the next unit to accumulate
-  int mg = lg;
-  int mkt = lkt;
-  int64_t mu = u0;
-  // B fragments of the chunk being multiplied; each register is refilled
-  // with the next chunk's fragment right after the kR MFMAs that read it,
-  // so the LDS reads of chunk c + 1 run under the MFMAs of chunk c and no
-  // MFMA waits for LDS.  A unit's partial flush comes before its MFMAs.
-  u32x4 b[kC][kNBT];
-  auto frag = [&](int stage, int j, int bt) __attribute__((always_inline)) {
-    return *reinterpret_cast<const u32x4*>(xs + ((stage * kC + j) * kNBT + bt) * 1024 + 16 * lane);
-  };
-  auto mma = [&](int stage, int next) __attribute__((always_inline)) {
-#pragma unroll
-    for (int j = 0; j < kC; ++j) {
-      if (mu < u1 && mkt == 0 && mu != u0) flush(mg - 1);
-      // a chunk past the range holds zeros in LDS and in its weight
-      // registers (both read outside their descriptors), so its MFMAs add
-      // exact zeros: no branch around them
-#pragma unroll
-      for (int bt = 0; bt < kNBT; ++bt) {
-#pragma unroll
-        for (int r = 0; r < kR; ++r)
-          acc[r][bt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[stage][j][r]),
-                                                               __builtin_bit_cast(bf16x8, b[j][bt]), acc[r][bt], 0, 0, 0);
-        b[j][bt] = frag(next, j, bt);
-      }
-#pragma unroll
-      for (int bt = 0; bt < kNBT; ++bt) {
-        __builtin_amdgcn_sched_group_barrier(0x008, kR, 0);  // the kR MFMAs of fragment bt
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // then its refill
-      }
-      ++mu;
-      if (++mkt == kt_count) {
-        mkt = 0;
-        ++mg;
-      }
-    }
-  };
-
-  // Chunks past the range load nothing (zero-size reads) and add zeros,
-  // so every chunk issues the same loads, the waits are fixed counts, and
-  // the ring is walked in whole turns (a range is padded by at most
-  // kStages - 1 such chunks): with a branch around each stage the compiler
-  // must allow for skipped stages, and it then waited for every load but
-  // the newest chunk's before the MFMAs, one chunk of prefetch whatever the
-  // depth.  The prologue keeps each chunk's loads in the loop's order
-  // (copies, then weights), so the first turn counts like the others.
-#pragma unroll
-  for (int s = 0; s < kD; ++s) {
-    issue(s);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  // chunk 0 in LDS for every wave, then its fragments into registers
-  __builtin_amdgcn_s_waitcnt(kWaitFirst);
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-#pragma unroll
-  for (int j = 0; j < kC; ++j)
-#pragma unroll
-    for (int bt = 0; bt < kNBT; ++bt) b[j][bt] = frag(0, j, bt);
-  for (int c0 = 0; c0 < nch; c0 += kStages) {
-#pragma unroll
-    for (int s = 0; s < kStages; ++s) {
-      // At chunk c = c0 + s: this wave's copies and weights of chunk c + 1
-      // have landed and its reads of chunk c's fragments are done; after the
-      // barrier every wave's copies of chunk c + 1 are in LDS and stage
-      // s - 1 (chunk c - 1, read during chunk c - 2) is free for chunk
-      // c + kD.  A bare s_barrier, fenced for the compiler only: a workgroup
-      // fence would also wait for the copies still in flight into the later
-      // stages.
-      __builtin_amdgcn_s_waitcnt(kWaitNext);
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      issue((s + kD) % kStages);
-      mma(s, (s + 1) % kStages);
-    }
-  }
-  if (u1 > u0) {
-    // the group of the range's last unit
-    const int64_t last = u1 - 1;
-    flush(static_cast<int>(last / kt_count));
-  }
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // copies into LDS still in flight end before the workgroup does
-}
-
-// y[b][rows[r]] for kRows rows: for each, the sum in workgroup order of the
-// partials of its row group (kSlots >= the plan's slots, the most
-// workgroups that touch one group).  All partial counts are worked out
-// first, under one uniform branch (32-bit arithmetic when every product
-// fits, as on 256 CUs for every supported shape; each 64-bit division is a
-// long instruction sequence), then every load is issued unconditionally:
-// slots past a group's count re-read its last slot and are dropped by a
-// select after the load.  As `j < cnt ? load : 0`, each load sat behind a
-// branch of its own and a lane waited for one row's partials before it
-// requested the next row's.
-template <int kSlots, int kRows>
-__device__ __forceinline__ void gemv_rows(const float* __restrict__ part, const GemvPlan& p, int batch, int b,
-                                          const int (&rows)[kRows], float (&y)[kRows]) {
-  int g[kRows], cnt[kRows];
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) g[r] = (rows[r] >> 4) / p.group;
-  if (((p.units * p.blocks) >> 32) == 0) {
-    const uint32_t nb = static_cast<uint32_t>(p.blocks), nu = static_cast<uint32_t>(p.units);
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      const uint32_t x0 = static_cast<uint32_t>(g[r]) * p.kt_count;
-      cnt[r] = static_cast<int>(((x0 + p.kt_count) * nb - 1) / nu - ((x0 + 1) * nb - 1) / nu + 1);
-    }
-  } else {
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      const int64_t x0 = static_cast<int64_t>(g[r]) * p.kt_count;
-      cnt[r] = static_cast<int>(((x0 + p.kt_count) * p.blocks - 1) / p.units - ((x0 + 1) * p.blocks - 1) / p.units + 1);
-    }
-  }
-  const int64_t slot_floats = static_cast<int64_t>(p.group) * batch * kTileRows;
-  float v[kRows][kSlots];
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    const int i = (rows[r] >> 4) - g[r] * p.group;
-    const float* q = part + static_cast<int64_t>(g[r]) * p.slots * slot_floats +
-                     (p.seq_major ? static_cast<int64_t>(b) * p.group + i : static_cast<int64_t>(i) * batch + b) *
-                         kTileRows +
-                     (rows[r] & 15);
-#pragma unroll
-    for (int j = 0; j < kSlots; ++j) v[r][j] = q[(j < cnt[r] ? j : cnt[r] - 1) * slot_floats];
-  }
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    float s = 0.f;
-#pragma unroll
-    for (int j = 0; j < kSlots; ++j) s += j < cnt[r] ? v[r][j] : 0.f;
-    y[r] = s;
-  }
-}
-
-// y[b][n .. n+3] for four consecutive rows n (n a multiple of 4, so one
-// 16-byte piece of one tile's partial row in every slot): the sum in
-// workgroup order of their group's partials, loaded as 16-byte pieces,
-// every slot's load issued before any is added.
-template <int kSlots>
-__device__ __forceinline__ float4 gemv_rows4(const float* __restrict__ part, const GemvPlan& p, int batch, int b,
-                                             int n) {
-  const int g = (n >> 4) / p.group;
-  int cnt;
-  if (((p.units * p.blocks) >> 32) == 0) {
-    const uint32_t nb = static_cast<uint32_t>(p.blocks), nu = static_cast<uint32_t>(p.units);
-    const uint32_t x0 = static_cast<uint32_t>(g) * p.kt_count;
-    cnt = static_cast<int>(((x0 + p.kt_count) * nb - 1) / nu - ((x0 + 1) * nb - 1) / nu + 1);
-  } else {
-    const int64_t x0 = static_cast<int64_t>(g) * p.kt_count;
-    cnt = static_cast<int>(((x0 + p.kt_count) * p.blocks - 1) / p.units - ((x0 + 1) * p.blocks - 1) / p.units + 1);
-  }
-  const int64_t slot_floats = static_cast<int64_t>(p.group) * batch * kTileRows;
-  const int i = (n >> 4) - g * p.group;
-  const float* q = part + static_cast<int64_t>(g) * p.slots * slot_floats +
-                   (p.seq_major ? static_cast<int64_t>(b) * p.group + i : static_cast<int64_t>(i) * batch + b) *
-                       kTileRows +
-                   (n & 15);
-  float4 v[kSlots];
-#pragma unroll
-  for (int j = 0; j < kSlots; ++j) v[j] = *reinterpret_cast<const float4*>(q + (j < cnt ? j : cnt - 1) * slot_floats);
-  float4 y = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-  for (int j = 0; j < kSlots; ++j)
-    if (j < cnt) {
-      y.x += v[j].x;
-      y.y += v[j].y;
-      y.z += v[j].z;
-      y.w += v[j].w;
-    }
-  return y;
-}
-
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) {
   return __builtin_bit_cast(float, static_cast<uint32_t>(h) << 16);
 }
@@ -621,9 +81,613 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
   return __builtin_bit_cast(uint16_t, static_cast<__bf16>(f));
 }
 
+// y[b, n] = sum_k x[b, k] W[n, k] over a packed W.  A workgroup takes RT row
+// tiles (16 rows each) x BT column tiles (16 sequences each) over the whole k
+// range, or one of a.splits parts of it.  Its W waves deal the 64-k pairs of
+// k tiles among themselves (wave w takes pairs w, w + W, ...), each with
+// accumulators for all RT x BT tiles, and add them in LDS at the end.
+//
+// What bounds it is what a CU can take in: RT x 16 weight rows from memory
+// and BT x 16 activation rows from L2, (16 RT + 16 BT) x k x 2 bytes a
+// workgroup.  Measured on this GPU: 26 bytes/ns and CU from memory with every
+// CU reading (6.7 TB/s), 50 with a quarter of them, whatever the depth; 104
+// from L2; and since a CU's loads return in order, 45-60 for a mix of the two
+// in small pieces.  Hence:
+//  * Activations go straight into LDS, 8 rows x 128 bytes per wave load
+//    (whole cache lines, consecutive lanes along a row): 104 bytes/ns, where
+//    loads in operand order (16 rows x 64 bytes, consecutive lanes in
+//    different rows) reach 38.  Lane l fetches the 16-byte piece
+//    (l % 8) ^ (l / 8) of row l / 8, so that the operand reads (16 or 32
+//    rows, one piece each) are free of bank conflicts.
+//  * Weights come in bursts of KB steps ahead of the block that uses them,
+//    not one step at a time: the L2 hits between two bursts then flow
+//    together (64 x 4096 -> 6144: 19.8 -> 17.1 us a call).
+//  * Every wave has a ring of DX steps of its own in LDS and two blocks of
+//    weights in registers: no barrier before the final sum.
+//  * The planner (plan_rows) picks the tile shape and the splits for the
+//    least of those bytes that still fills the CUs.
+// A stream-K split over workgroups of 8 row tiles, which this replaces, read
+// its activations in operand order or behind a barrier per chunk and passed
+// 9 MB of fp32 partials at 64 sequences, 38 MB at 256, to the epilogue.
+// Whole calls replayed from a graph, cold weights, before -> now: prelude
+// 64 x 4096 -> 6144 19.9 -> 17.1 us, 256 x 5120 -> 7168 48 -> 39, 16 x 3072
+// -> 5120 13.4 -> 9.8, 4 x 8192 -> 10240 32.1 -> 31.2; o_proj 100 x 5120 ->
+// 5120 28.3 -> 24.4, 4 x 8192 -> 8192 29.0 -> 26.5, 200 x 3072 -> 3072
+// 26.8 -> 17.7.
+//
+// Columns at or past the batch and k at or past the end read as zeros
+// (outside the descriptors), as do steps past a wave's last pair: every wave
+// of the workgroup takes the same number of blocks with fixed wait counts.
+struct NoEpilogue {};
+
+// waves per SIMD the register budget is set for
+constexpr int rows_min_waves(int rt, int bt, int w, int kb) { return w > 4 ? (rt * bt * kb <= 4 ? 4 : 2) : 1; }
+// s_waitcnt vmcnt(n) alone; vmcnt is split over bits 3:0 and 15:14
+constexpr int kWaitLoads = 0x0F70;
+constexpr int wait_loads(int n) { return kWaitLoads | (n & 15) | ((n >> 4) << 14); }
+__host__ __device__ constexpr int rows_lds_bytes(int rt, int bt, int w, int dx) {
+  const int ring = w * dx * bt * 2048, sum = w * rt * bt * 1024;
+  return ring > sum ? ring : sum;
+}
+
+// N consecutive bf16 values, packed two to a register; p need only be 2-byte
+// aligned (the memory pipeline takes any alignment).
+template <int N>
+__device__ __forceinline__ void load_bf16(const uint16_t* p, uint32_t* v) {
+  __builtin_memcpy(v, p, 2 * N);
+}
+__device__ __forceinline__ float unpack_bf16(const uint32_t* v, int j) {
+  return bf16_to_f32(static_cast<uint16_t>(v[j / 2] >> (16 * (j & 1))));
+}
+template <int N>
+__device__ __forceinline__ void store_bf16(uint16_t* p, const float (&v)[N]) {
+  uint32_t w[N / 2];
+#pragma unroll
+  for (int j = 0; j < N / 2; ++j)
+    w[j] = f32_to_bf16(v[2 * j]) | (static_cast<uint32_t>(f32_to_bf16(v[2 * j + 1])) << 16);
+  __builtin_memcpy(p, w, 2 * N);
+}
+
+// Sine and cosine of position pos at rotary pair i0 + j, j < N (i0 a multiple
+// of N): the angle p * theta^(-2i/r), in turns, in fp64 (positions reach 10^5
+// and more, where an fp32 angle would already be off by ~10^-2 rad); its
+// fraction in [-1/2, 1/2] goes to the hardware sine and cosine, which take
+// turns.  The frequency is the product of the host's theta^(-2 * 2^k / r)
+// over the set bits k of i.
+template <int N>
+__device__ __forceinline__ void rope_angles(const PreludeArgs& a, int pos, int i0, float (&sn)[N], float (&cs)[N]) {
+  constexpr double kInvTwoPi = 0.15915494309189535;
+  constexpr int kLow = N == 4 ? 2 : (N == 2 ? 1 : 0);
+  double base = static_cast<double>(pos) * kInvTwoPi;
+#pragma unroll
+  for (int k = kLow; k < 8; ++k) base = (i0 >> k) & 1 ? base * a.freq_pow2[k] : base;
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    double t = base;
+    if (j & 1) t *= a.freq_pow2[0];
+    if (j & 2) t *= a.freq_pow2[1];
+    const float frac = static_cast<float>(t - __builtin_rint(t));
+    sn[j] = __builtin_amdgcn_sinf(frac);
+    cs[j] = __builtin_amdgcn_cosf(frac);
+  }
+}
+
+__device__ __forceinline__ int clamped(int x, int most) { return x < 0 ? 0 : (x > most ? most : x); }
+
+template <int RT, int BT, int W, int DX, int KB, bool kWide, bool kShared, class Epilogue>
+__global__ __launch_bounds__(W * 64, rows_min_waves(RT, BT, W, KB)) void rows_kernel(RowsArgs a, Epilogue e) {
+  constexpr bool kPrelude = std::is_same<Epilogue, PreludeArgs>::value;
+  constexpr bool kResidual = std::is_same<Epilogue, OProjArgs>::value;
+  static_assert(KB % DX == 0, "a block of weights covers whole turns of the activation ring");
+  static_assert(!kPrelude || RT % 2 == 0, "the prelude's row tiles go in pairs");
+  static_assert(!kWide || (RT % 2 == 0 && BT % 2 == 0), "wide tiles take row and column tiles in pairs");
+  constexpr int kSlot = BT * 2048;               // one step's activations of a wave
+  constexpr int kLx = 2 * BT, kLw = 2 * RT;      // vector memory instructions of a step
+  constexpr uint32_t kOutside = 0x80000000u;     // past any descriptor: reads zero
+  // matrix-core tiles, kTR x kTC of 16 x 16 x 32 or, with kWide, of
+  // 32 x 32 x 16 (two row tiles x two column tiles); kTM of them cover a
+  // step's k, and an accumulator is kTG groups of four rows per lane
+  constexpr int kTR = kWide ? RT / 2 : RT, kTC = kWide ? BT / 2 : BT;
+  constexpr int kTM = kWide ? 4 : 2, kTG = kWide ? 4 : 1;
+  using Acc = typename std::conditional<kWide, f32x16, f32x4>::type;
+  // epilogue items: a group of one accumulator, or for the prelude the same
+  // group of both row tiles of a pair; half the rows of each lane where
+  // there are fewer groups than waves
+  constexpr int kUnits = kTR * kTC * kTG / (kPrelude ? 2 : 1);
+  constexpr int kSub = kUnits < W ? 2 : 1;
+  constexpr int kRows = 4 / kSub;                // rows per lane of an item
+  constexpr int kItems = kUnits * kSub;
+  constexpr int kPer = (kItems + W - 1) / W;     // items per wave, at most
+  extern __shared__ __align__(1024) unsigned char xs[];
+
+  const int lane = threadIdx.x & 63;
+  const int wv = uniform(threadIdx.x >> 6);
+  const int col = kWide ? lane & 31 : lane & 15;   // of a tile: operand row or column, result column
+  const int kblk = kWide ? lane >> 5 : lane >> 4;  // operand k block of 8, result row block of 4
+  const int k = a.k;
+  const int kt_count = k / kTileK;
+  // k split `sp` of a.splits (NoEpilogue only): whole pairs [pair0, pair1)
+  const int sp = a.splits > 1 ? static_cast<int>(blockIdx.x) / a.split_grid : 0;
+  const int blk0 = static_cast<int>(blockIdx.x) - sp * a.split_grid;
+  int rg = blk0, bg = 0;
+  if constexpr (kShared) {
+    // workgroups go to the XCDs round-robin: those of one row group take
+    // consecutive places of one XCD, so that its weights come from memory
+    // once and from that XCD's L2 after that
+    const int i = blk0 >> 3;
+    const int q = i / a.col_groups;
+    rg = q * 8 + (blk0 & 7);
+    bg = i - q * a.col_groups;
+    if (rg >= a.row_groups) return;
+  }
+  const int tile0 = rg * RT;                     // first row tile (or first pair x 2)
+  const int b0 = bg * BT * 16;                   // first sequence
+  const int tiles = a.n / kTileRows;
+
+  // Item `it`: accumulator column c; row tile r of the workgroup (with the
+  // prelude, pair r) and the lane's first row in it.
+  struct Item {
+    int c, r, row0, acc_r, group, sub;
+  };
+  auto item_of = [&](int it) __attribute__((always_inline)) {
+    Item m;
+    const int u = it / kSub;
+    m.sub = it % kSub;
+    constexpr int kG = kWide ? (kPrelude ? 2 : 4) : 1;  // groups of an accumulator taken one by one
+    m.group = u % kG;
+    m.c = (u / kG) % kTC;
+    const int x = u / kG / kTC;
+    m.acc_r = x;
+    m.r = kWide && !kPrelude ? 2 * x + (m.group >> 1) : x;
+    m.row0 = (kWide ? 8 * (m.group & 1) : 0) + 4 * kblk + m.sub * kRows;
+    return m;
+  };
+
+  // ---- what the epilogue reads beside the sums, requested first
+  int item_b[kPer];
+  bool item_on[kPer];
+  float sn[kPer][kRows], cs[kPer][kRows];
+  // residual, or bias of the pair's rows: kept as loaded and converted after
+  // the loop, so that nothing waits for them here
+  uint32_t raw[kPer][kPrelude ? kRows : kRows / 2];
+  int pos[kPer];
+#pragma unroll
+  for (int t = 0; t < kPer; ++t) {
+    const int it = wv + t * W;
+    const Item m = item_of(it);
+    item_b[t] = b0 + (kWide ? 32 : 16) * m.c + col;
+    item_on[t] = it < kItems && item_b[t] < a.batch;
+    if constexpr (kPrelude) pos[t] = item_on[t] ? e.lens[item_b[t]] : 0;
+    if constexpr (kResidual) {
+      const int n = 16 * (tile0 + m.r) + m.row0;
+      item_on[t] = item_on[t] && n < a.n;
+#pragma unroll
+      for (int j = 0; j < kRows / 2; ++j) raw[t][j] = 0u;
+      if (item_on[t]) load_bf16<kRows>(e.residual + static_cast<int64_t>(item_b[t]) * a.n + n, raw[t]);
+    }
+  }
+
+  // ---- load streams
+  const __amdgpu_buffer_rsrc_t rx = make_rsrc(a.x, static_cast<uint32_t>(a.batch) * k * 2u);
+  const int xrow = lane >> 3;
+  const int xpiece = (lane & 7) ^ xrow;
+  const uint32_t xlane = static_cast<uint32_t>(b0 + xrow) * k * 2u + xpiece * 16u;
+  const uint32_t xstep8 = static_cast<uint32_t>(k) * 16u;  // bytes of 8 rows
+  unsigned char* ring = xs + wv * (DX * kSlot);
+  // row tile r of the workgroup; a prelude pair's second tile holds the
+  // rotation partners of its first
+  auto tile_of = [&](int r) __attribute__((always_inline)) {
+    int t = tile0 + r;
+    if constexpr (kPrelude) {
+      // pair q of a head of d / 16 tiles, rotated in halves over r dims:
+      // tiles (q, q + r / 32) for q < r / 32, then and otherwise (2q, 2q + 1)
+      const int per_head = e.d / 32;
+      const int pair = t >> 1;
+      const int h = pair / per_head, q = pair - h * per_head;
+      const int half = (!e.interleaved && h < e.hq + e.hkv) ? e.rotary_dim / 32 : 0;
+      t = h * 2 * per_head + (q < half ? q + (r & 1) * half : 2 * q + (r & 1));
+    }
+    return uniform(t);
+  };
+  // one descriptor per row tile, or (wide) per two, the second `wdelta` on
+  __amdgpu_buffer_rsrc_t rw[kTR];
+  uint32_t wlane[kTR];
+#pragma unroll
+  for (int r = 0; r < kTR; ++r) {
+    const int t = tile_of(kWide ? 2 * r : r);
+    const int t2 = kWide ? tile_of(2 * r + 1) : t;
+    const uint32_t delta = static_cast<uint32_t>(t2 - t) * kt_count * 1024u;
+    // tiles past the last row are outside: both, or (wide) the second alone
+    const uint32_t bytes = t2 < tiles ? delta + kt_count * 1024u : (t < tiles ? kt_count * 1024u : 0u);
+    rw[r] = make_rsrc(a.wp + static_cast<int64_t>(t < tiles ? t : 0) * kt_count * (kTileRows * kTileK), bytes);
+    wlane[r] = kWide ? (lane & 16 ? delta : 0u) + (16 * kblk + (lane & 15)) * 16u : lane * 16u;
+  }
+  const int pairs = (kt_count + 1) / 2;
+  const int pair0 = a.splits > 1 ? sp * pairs / a.splits : 0;
+  const int pair1 = a.splits > 1 ? (sp + 1) * pairs / a.splits : pairs;
+  const int k_end = pair1 * kPairK < k ? pair1 * kPairK : k;
+  const int kt_end = pair1 * 2 < kt_count ? pair1 * 2 : kt_count;
+  const int steps = (pair1 - pair0 + W - 1) / W;
+
+  auto issue_x = [&](int slot, int s) __attribute__((always_inline)) {
+    const int k0 = (pair0 + wv + s * W) * kPairK;
+    const uint32_t off = (k0 + 8 * xpiece < k_end ? xlane : kOutside) + k0 * 2u;
+#pragma unroll
+    for (int i = 0; i < kLx; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rx, (__attribute__((address_space(3))) void*)(ring + slot * kSlot + i * 1024), 16, off + i * xstep8, 0, 0, 0);
+  };
+  // the weights of block blk (KB steps); k tiles past the end are outside
+  u32x4 wa[2][KB][kTR][kTM];
+  auto issue_w = [&](int buf, int blk) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < KB; ++i) {
+      const int kt = 2 * (pair0 + wv + (blk * KB + i) * W);
+      uint32_t at[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) at[j] = kt + j < kt_end ? static_cast<uint32_t>(kt + j) * 1024u : kOutside;
+#pragma unroll
+      for (int r = 0; r < kTR; ++r)
+#pragma unroll
+        for (int m = 0; m < kTM; ++m)
+          wa[buf][i][r][m] = __builtin_amdgcn_raw_buffer_load_b128(
+              rw[r], wlane[r] + at[kWide ? m >> 1 : m] + (kWide ? (m & 1) * 512 : 0), 0, kShared ? 0 : kCachePolicyNT);
+    }
+  };
+
+  Acc acc[kTR][kTC];
+#pragma unroll
+  for (int r = 0; r < kTR; ++r)
+#pragma unroll
+    for (int c = 0; c < kTC; ++c) acc[r][c] = Acc{};
+  // operand m of accumulator column c: row `col`, piece (pieces per m) m + kblk
+  const int frag0 = (col >> 3) * 1024 + (col & 7) * 128 + ((kblk ^ (col & 7)) * 16);
+  u32x4 xb[kTC][kTM];
+  auto operands = [&](int slot) __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int c = 0; c < kTC; ++c)
+#pragma unroll
+      for (int m = 0; m < kTM; ++m)
+        xb[c][m] = *reinterpret_cast<const u32x4*>(ring + slot * kSlot + c * (kSlot / kTC) + (frag0 ^ (m * (128 / kTM))));
+  };
+  // the slot takes the activations DX steps on once its operands are in registers
+  auto refill = [&](int slot, int s) __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+    issue_x(slot, s + DX);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto multiply = [&](int buf, int i) __attribute__((always_inline)) {
+#pragma unroll
+    for (int m = 0; m < kTM; ++m)
+#pragma unroll
+      for (int c = 0; c < kTC; ++c)
+#pragma unroll
+        for (int r = 0; r < kTR; ++r) {
+          const bf16x8 w = __builtin_bit_cast(bf16x8, wa[buf][i][r][m]), v = __builtin_bit_cast(bf16x8, xb[c][m]);
+          if constexpr (kWide)
+            acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, v, acc[r][c], 0, 0, 0);
+          else
+            acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, v, acc[r][c], 0, 0, 0);
+        }
+  };
+
+  issue_w(0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int s = 0; s < DX; ++s) issue_x(s, s);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // while the first loads are in flight: rotary angles, bias, page ids
+  uint32_t page_id[kPer];  // block-table entry of the appended token
+  if constexpr (kPrelude) {
+    const int per_head = e.d / 32;
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+      const Item m = item_of(wv + t * W);
+      const int pair = (tile0 >> 1) + m.r;
+      const int h = pair / per_head, q = pair - h * per_head;
+      const int p = pos[t] > 0 ? pos[t] - 1 : 0;
+      page_id[t] = 0u;
+      item_on[t] = item_on[t] && h < e.hq + 2 * e.hkv;
+      const bool turned = h < e.hq + e.hkv;
+      int tA = 2 * q, tB = 2 * q + 1;
+      if (!e.interleaved && turned && q < e.rotary_dim / 32) tA = q, tB = q + e.rotary_dim / 32;
+      if (item_on[t] && turned) {
+        if (e.interleaved) {
+          float s2[kRows / 2], c2[kRows / 2], s3[kRows / 2], c3[kRows / 2];
+          rope_angles<kRows / 2>(e, p, (16 * tA + m.row0) / 2, s2, c2);
+          rope_angles<kRows / 2>(e, p, (16 * tB + m.row0) / 2, s3, c3);
+#pragma unroll
+          for (int j = 0; j < kRows / 2; ++j) {
+            sn[t][j] = s2[j], cs[t][j] = c2[j];
+            sn[t][kRows / 2 + j] = s3[j], cs[t][kRows / 2 + j] = c3[j];
+          }
+        } else {
+          rope_angles<kRows>(e, p, 16 * tA + m.row0, sn[t], cs[t]);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < kRows; ++j) raw[t][j] = 0u;
+      if (e.bias && item_on[t]) {
+        load_bf16<kRows>(e.bias + h * e.d + 16 * tA + m.row0, raw[t]);
+        load_bf16<kRows>(e.bias + h * e.d + 16 * tB + m.row0, raw[t] + kRows / 2);
+      }
+      if (e.k_cache && item_on[t] && h >= e.hq) {
+        const int at = clamped(pos[t], e.maxp << e.page_shift) - 1;
+        if (at >= 0) page_id[t] = static_cast<uint32_t>(e.bt[static_cast<int64_t>(item_b[t]) * e.maxp + (at >> e.page_shift)]);
+      }
+    }
+  }
+
+  // A block issues the next block's weights, then per step waits for the
+  // step's activations (and so for every older load, its weights among
+  // them), reads them, requests those of DX steps on and multiplies.  The
+  // last block issues no weights, and what it waits for is all that is in
+  // flight (a fixed count would not do there: the compiler drops loads whose
+  // results no later step uses).
+  auto block = [&](int buf, int blk, auto last) __attribute__((always_inline)) {
+    constexpr bool kLast = decltype(last)::value;
+    if constexpr (!kLast) {
+      issue_w(buf ^ 1, blk + 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int j = 0; j < KB; ++j) {
+      if constexpr (kLast) {
+        if (j == 0 || j >= DX) __builtin_amdgcn_s_waitcnt(kWaitLoads);
+      } else {
+        // younger than the step's activations: those of the DX - 1 steps
+        // after it, and the block's weights where they were issued before
+        constexpr int kEarly = (DX - 1) * kLx + KB * kLw, kLate = (DX - 1) * kLx;
+        static_assert(kEarly < 64, "vmcnt holds at most 63");
+        if (j < DX)
+          __builtin_amdgcn_s_waitcnt(wait_loads(kEarly));
+        else
+          __builtin_amdgcn_s_waitcnt(wait_loads(kLate));
+      }
+      operands(j % DX);
+      if (!kLast || j + DX < KB) refill(j % DX, blk * KB + j);
+      multiply(buf, j);
+    }
+  };
+  const int blocks = (steps + KB - 1) / KB;
+  int blk = 0;
+  for (; blk + 2 < blocks; blk += 2) {
+    block(0, blk, std::false_type{});
+    block(1, blk + 1, std::false_type{});
+  }
+  if (blk + 1 < blocks) {
+    block(0, blk, std::false_type{});
+    block(1, blk + 1, std::true_type{});
+  } else {
+    block(0, blk, std::true_type{});
+  }
+
+  // ---- the waves' sums meet in LDS
+  __builtin_amdgcn_s_waitcnt(kWaitLoads);  // copies into the rings (zeros past the end) are done
+  __syncthreads();
+  f32x4* red = reinterpret_cast<f32x4*>(xs);  // [W][kTR][kTC][kTG][64 lanes]
+#pragma unroll
+  for (int r = 0; r < kTR; ++r)
+#pragma unroll
+    for (int c = 0; c < kTC; ++c)
+#pragma unroll
+      for (int g = 0; g < kTG; ++g)
+        red[(((wv * kTR + r) * kTC + c) * kTG + g) * 64 + lane] =
+            f32x4{acc[r][c][4 * g], acc[r][c][4 * g + 1], acc[r][c][4 * g + 2], acc[r][c][4 * g + 3]};
+  __syncthreads();
+  auto total = [&](int r, int c, int g, int sub, float (&v)[kRows]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) v[j] = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const float* p = reinterpret_cast<const float*>(red + (((w * kTR + r) * kTC + c) * kTG + g) * 64 + lane) + sub * kRows;
+#pragma unroll
+      for (int j = 0; j < kRows; ++j) v[j] += p[j];
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < kPer; ++t) {
+    const int it = wv + t * W;
+    if (kItems % W != 0 && it >= kItems) break;
+    const Item m = item_of(it);
+    const int64_t b = item_b[t];
+    if constexpr (kPrelude) {
+      // the pair's tiles: two accumulators, or two groups of one
+      float v[2][kRows];
+      total(kWide ? m.acc_r : 2 * m.acc_r, m.c, m.group, m.sub, v[0]);
+      total(kWide ? m.acc_r : 2 * m.acc_r + 1, m.c, kWide ? m.group + 2 : 0, m.sub, v[1]);
+      const int per_head = e.d / 32;
+      const int pair = (tile0 >> 1) + m.r;
+      const int h = pair / per_head, q = pair - h * per_head;
+      const bool turned = h < e.hq + e.hkv;
+      const bool halves = !e.interleaved && turned && q < e.rotary_dim / 32;
+      const int eA = 16 * (halves ? q : 2 * q) + m.row0;
+      const int eB = 16 * (halves ? q + e.rotary_dim / 32 : 2 * q + 1) + m.row0;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) v[i][j] += unpack_bf16(raw[t] + i * (kRows / 2), j);
+      if (halves) {
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) {
+          const float x0 = v[0][j], x1 = v[1][j];
+          v[0][j] = x0 * cs[t][j] - x1 * sn[t][j];
+          v[1][j] = x1 * cs[t][j] + x0 * sn[t][j];
+        }
+      } else if (e.interleaved && turned) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < kRows; j += 2) {
+            const int ei = (i ? eB : eA) + j;
+            const float c1 = cs[t][i * (kRows / 2) + j / 2], s1 = sn[t][i * (kRows / 2) + j / 2];
+            const float x0 = v[i][j], x1 = v[i][j + 1];
+            if (ei < e.rotary_dim) {
+              v[i][j] = x0 * c1 - x1 * s1;
+              v[i][j + 1] = x1 * c1 + x0 * s1;
+            }
+          }
+      }
+      if (!item_on[t]) continue;
+      uint16_t* dst = nullptr;
+      if (h < e.hq) {
+        dst = e.q_out + (b * e.hq + h) * e.d;
+      } else {
+        const bool is_k = turned;
+        const int g = is_k ? h - e.hq : h - e.hq - e.hkv;
+        uint16_t* out = is_k ? e.k_out : e.v_out;
+        if (out) dst = out + (b * e.hkv + g) * e.d;
+        const int at = clamped(pos[t], e.maxp << e.page_shift) - 1;
+        if (e.k_cache && at >= 0) {  // length 0: no token in this slot, nothing to append
+          const int64_t page = page_id[t] < static_cast<uint32_t>(e.num_pages) ? page_id[t] : e.num_pages - 1;
+          const int64_t row = (page << e.page_shift) + (at & ((1 << e.page_shift) - 1));
+          uint16_t* cache = (is_k ? e.k_cache : e.v_cache) + (row * e.hkv + g) * e.d;
+          store_bf16<kRows>(cache + eA, v[0]);
+          store_bf16<kRows>(cache + eB, v[1]);
+        }
+      }
+      if (dst) {
+        store_bf16<kRows>(dst + eA, v[0]);
+        store_bf16<kRows>(dst + eB, v[1]);
+      }
+    } else {
+      const int tile = tile0 + m.r;
+      const int n = 16 * tile + m.row0;
+      float v[kRows];
+      total(m.acc_r, m.c, m.group, m.sub, v);
+      if constexpr (kResidual) {
+        float ss = 0.f;
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) {
+          v[j] += unpack_bf16(raw[t], j);
+          ss += v[j] * v[j];
+        }
+        // over the lanes of one column: a row tile, or half of one (wide)
+        if constexpr (!kWide) ss += __shfl_xor(ss, 16);
+        ss += __shfl_xor(ss, 32);
+        constexpr int kParts = rows_ss_parts(RT, BT, W, kWide);
+        const int part = kWide ? (m.group & 1) * kSub + m.sub : m.sub;
+        if (item_on[t] && kblk == 0) e.ss[b * e.ss_count + tile * kParts + part] = ss;
+      }
+      if (b < a.batch && n < a.n) {
+        float* p = a.y + (static_cast<int64_t>(sp) * a.batch + b) * a.n + n;
+        if constexpr (kRows == 4)
+          *reinterpret_cast<f32x4*>(p) = f32x4{v[0], v[1], v[2], v[3]};
+        else
+          *reinterpret_cast<float2*>(p) = make_float2(v[0], v[1]);
+      }
+    }
+  }
+}
+
+// Second kernel of o_proj: workgroup (sequence b, chunk of kNormFeatures
+// features) adds the sequence's partial sums of z^2 (ss_count of them, in a
+// fixed order) and writes residual_out = bf16(z) and
+// normed_out = z / sqrt(mean + eps) * w for its chunk.  z and the weights
+// are requested before the sums are used.
+__global__ __launch_bounds__(kNormThreads) void oproj_norm_kernel(OProjArgs a) {
+  __shared__ float wsum[kNormThreads / 64];
+  const int chunks = (a.hidden + kNormFeatures - 1) / kNormFeatures;
+  const int b = blockIdx.x / chunks;
+  const int c = blockIdx.x - b * chunks;
+  const int tid = threadIdx.x;
+  const int n = c * kNormFeatures + 4 * tid;
+  const bool in = n < a.hidden;
+  const int64_t at = static_cast<int64_t>(b) * a.hidden + n;
+  float z[4] = {0.f, 0.f, 0.f, 0.f};
+  uint32_t w[2] = {0u, 0u};
+  if (in) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(a.z + at);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) z[j] = v[j];
+    load_bf16<4>(a.norm_w + n, w);
+  }
+  const float* ss = a.ss + static_cast<int64_t>(b) * a.ss_count;
+  float t = 0.f;
+#pragma unroll 4
+  for (int i = tid; i < a.ss_count; i += kNormThreads) t += ss[i];
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off);
+  if ((tid & 63) == 0) wsum[tid >> 6] = t;
+  __syncthreads();
+  float tot = 0.f;
+#pragma unroll
+  for (int i = 0; i < kNormThreads / 64; ++i) tot += wsum[i];
+  const float inv = rsqrtf(tot / a.hidden + a.eps);
+  if (!in) return;
+  float h[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) h[j] = z[j] * inv * unpack_bf16(w, j);
+  store_bf16<4>(a.residual_out + at, z);
+  store_bf16<4>(a.normed_out + at, h);
+}
+
+// Second kernel of o_proj where the projection was split along k: one
+// workgroup per sequence b adds the splits' partials (in order) and the
+// residual, kept in registers (hidden <= kSumFeatures), reduces the sum of
+// z^2 in a fixed order and writes both outputs.
+__global__ __launch_bounds__(kSumThreads) void oproj_sum_kernel(OProjArgs a) {
+  constexpr int kGroups = kSumFeatures / (4 * kSumThreads);
+  __shared__ float wsum[kSumThreads / 64];
+  const int b = blockIdx.x;
+  const int tid = threadIdx.x;
+  const int64_t base = static_cast<int64_t>(b) * a.hidden;
+  const int64_t stride = static_cast<int64_t>(a.batch) * a.hidden;
+  float z[kGroups][4];
+  uint32_t w[kGroups][2];
+  float ss = 0.f;
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) {
+    const int n = 4 * (tid + kSumThreads * g);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) z[g][j] = 0.f;
+    w[g][0] = w[g][1] = 0u;
+    if (n < a.hidden) {
+      uint32_t r[2];
+      load_bf16<4>(a.norm_w + n, w[g]);
+      load_bf16<4>(a.residual + base + n, r);
+      f32x4 part[kMaxRowsSplits];
+#pragma unroll
+      for (int s = 0; s < kMaxRowsSplits; ++s)
+        part[s] = *reinterpret_cast<const f32x4*>(a.z + (s < a.splits ? s : a.splits - 1) * stride + base + n);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float y = part[0][j];
+#pragma unroll
+        for (int s = 1; s < kMaxRowsSplits; ++s) y += s < a.splits ? part[s][j] : 0.f;
+        z[g][j] = y + unpack_bf16(r, j);
+        ss += z[g][j] * z[g][j];
+      }
+      store_bf16<4>(a.residual_out + base + n, z[g]);
+    }
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off);
+  if ((tid & 63) == 0) wsum[tid >> 6] = ss;
+  __syncthreads();
+  float tot = 0.f;
+#pragma unroll
+  for (int i = 0; i < kSumThreads / 64; ++i) tot += wsum[i];
+  const float inv = rsqrtf(tot / a.hidden + a.eps);
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) {
+    const int n = 4 * (tid + kSumThreads * g);
+    if (n < a.hidden) {
+      float h[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) h[j] = z[g][j] * inv * unpack_bf16(w[g], j);
+      store_bf16<4>(a.normed_out + base + n, h);
+    }
+  }
+}
+
 // One wave per (sequence b, head h) of the projection: h < hq is a q head,
 // then hkv k heads, then hkv v heads.  Lane owns elements lane + 64 j.
-template <int D, int kSlots>
+template <int D>
 __global__ __launch_bounds__(64) void prelude_epilogue(PreludeArgs a) {
   constexpr int E = D / 64;
   __shared__ float s[D];
@@ -659,18 +723,26 @@ __global__ __launch_bounds__(64) void prelude_epilogue(PreludeArgs a) {
   // bias and norm weights are loaded whether present or not (from the
   // partials, a valid address, when absent; dropped by a select), so that
   // no load waits behind a branch
-  const uint16_t* bias_p = a.bias ? a.bias + h * D : reinterpret_cast<const uint16_t*>(a.part);
-  const uint16_t* nw_p = nw ? nw : reinterpret_cast<const uint16_t*>(a.part);
-  int rows[E];
+  const float* y = a.y + (static_cast<int64_t>(b) * heads + h) * D;
+  const int64_t split_stride = static_cast<int64_t>(a.batch) * heads * D;
+  const uint16_t* bias_p = a.bias ? a.bias + h * D : reinterpret_cast<const uint16_t*>(a.y);
+  const uint16_t* nw_p = nw ? nw : reinterpret_cast<const uint16_t*>(a.y);
   float v[E];
   uint16_t bias_h[E], wn_h[E];
 #pragma unroll
   for (int j = 0; j < E; ++j) {
-    rows[j] = h * D + lane + 64 * j;
+    // every split's partial is requested before any is added; splits past
+    // the last re-read it and are dropped
+    float part[kMaxRowsSplits];
+#pragma unroll
+    for (int s2 = 0; s2 < kMaxRowsSplits; ++s2)
+      part[s2] = y[lane + 64 * j + (s2 < a.splits ? s2 : a.splits - 1) * split_stride];
+    v[j] = part[0];
+#pragma unroll
+    for (int s2 = 1; s2 < kMaxRowsSplits; ++s2) v[j] += s2 < a.splits ? part[s2] : 0.f;
     bias_h[j] = bias_p[lane + 64 * j];
     wn_h[j] = nw_p[lane + 64 * j];
   }
-  gemv_rows<kSlots>(a.part, a.plan, a.batch, b, rows, v);
 #pragma unroll
   for (int j = 0; j < E; ++j) v[j] += a.bias ? bf16_to_f32(bias_h[j]) : 0.f;
   if (nw) {
@@ -765,242 +837,7 @@ __global__ __launch_bounds__(64) void prelude_epilogue(PreludeArgs a) {
   }
 }
 
-// Pass 1, one workgroup per (sequence b, chunk c of features), one feature
-// per thread: z = y + residual (fp32 to scratch, bf16 to residual_out) and
-// the chunk's sum of z^2 (fixed reduction order).  residual_out may be the
-// residual buffer: each feature is read and written by the same thread.
-template <int kSlots>
-__global__ __launch_bounds__(kOProjChunk) void oproj_residual_kernel(OProjArgs a) {
-  __shared__ float wsum[kOProjChunk / 64];
-  const int chunks = oproj_chunks(a.hidden);
-  const int b = blockIdx.x / chunks;
-  const int c = blockIdx.x - b * chunks;
-  const int n = c * kOProjChunk + threadIdx.x;
-  const int64_t at = static_cast<int64_t>(b) * a.hidden + n;
-  float z = 0.f;
-  if (n < a.hidden) {
-    const int rows[1] = {n};
-    float y[1];
-    gemv_rows<kSlots>(a.part, a.plan, a.batch, b, rows, y);
-    z = y[0] + bf16_to_f32(a.residual[at]);
-    a.z[at] = z;
-    a.residual_out[at] = f32_to_bf16(z);
-  }
-  float ss = z * z;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off);
-  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float t = 0.f;
-#pragma unroll
-    for (int i = 0; i < kOProjChunk / 64; ++i) t += wsum[i];
-    a.chunk_ss[static_cast<int64_t>(b) * chunks + c] = t;
-  }
-}
-
-// Pass 2, same grid: the sequence's total (chunk sums in chunk order) and
-// h = z / sqrt(mean + eps) * w.
-__global__ __launch_bounds__(kOProjChunk) void oproj_norm_kernel(OProjArgs a) {
-  const int chunks = oproj_chunks(a.hidden);
-  const int b = blockIdx.x / chunks;
-  const int c = blockIdx.x - b * chunks;
-  const int n = c * kOProjChunk + threadIdx.x;
-  if (n >= a.hidden) return;
-  // z and the weight are requested before the chunk sums (scalar loads,
-  // eight in flight at a time), whose latency hides theirs
-  const int64_t at = static_cast<int64_t>(b) * a.hidden + n;
-  const float z = a.z[at];
-  const float w = bf16_to_f32(a.norm_w[n]);
-  const float* ss = a.chunk_ss + static_cast<int64_t>(b) * chunks;
-  float tot = 0.f;
-#pragma unroll 8
-  for (int i = 0; i < chunks; ++i) tot += ss[i];
-  const float inv = rsqrtf(tot / a.hidden + a.eps);
-  a.normed_out[at] = f32_to_bf16(z * inv * w);
-}
-
-// The o_proj epilogue in one kernel for small batches, one workgroup per
-// sequence b; thread t takes the four consecutive features 4 (t + 1024 j):
-// z = y + residual kept in registers (fp32; bf16 to residual_out), the
-// sequence's sum of z^2 reduced across the workgroup in a fixed order,
-// then h = z / sqrt(mean + eps) * w.  Partials are read as 16-byte pieces.
-template <int kSlots>
-__global__ __launch_bounds__(kOProjOneThreads) void oproj_one_kernel(OProjArgs a) {
-  constexpr int kGroups = kOProjOneFeatures / 4;  // groups of four features per thread, at most
-  __shared__ float wsum[kOProjOneThreads / 64];
-  const int b = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int64_t base = static_cast<int64_t>(b) * a.hidden;
-  float4 z[kGroups];
-  uint2 w[kGroups];  // norm weights, requested with everything else before the reduction
-  float ss = 0.f;
-#pragma unroll
-  for (int j = 0; j < kGroups; ++j) {
-    const int n = 4 * (tid + kOProjOneThreads * j);
-    z[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-    w[j] = make_uint2(0u, 0u);
-    if (n < a.hidden) {
-      w[j] = *reinterpret_cast<const uint2*>(a.norm_w + n);
-      const uint2 r = *reinterpret_cast<const uint2*>(a.residual + base + n);
-      const float4 y = gemv_rows4<kSlots>(a.part, a.plan, a.batch, b, n);
-      z[j] = make_float4(y.x + bf16_to_f32(static_cast<uint16_t>(r.x)), y.y + bf16_to_f32(static_cast<uint16_t>(r.x >> 16)),
-                         y.z + bf16_to_f32(static_cast<uint16_t>(r.y)), y.w + bf16_to_f32(static_cast<uint16_t>(r.y >> 16)));
-      ss += z[j].x * z[j].x + z[j].y * z[j].y + z[j].z * z[j].z + z[j].w * z[j].w;
-      uint2 o;
-      o.x = f32_to_bf16(z[j].x) | (static_cast<uint32_t>(f32_to_bf16(z[j].y)) << 16);
-      o.y = f32_to_bf16(z[j].z) | (static_cast<uint32_t>(f32_to_bf16(z[j].w)) << 16);
-      *reinterpret_cast<uint2*>(a.residual_out + base + n) = o;
-    }
-  }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off);
-  if ((tid & 63) == 0) wsum[tid >> 6] = ss;
-  __syncthreads();
-  float tot = 0.f;
-#pragma unroll
-  for (int i = 0; i < kOProjOneThreads / 64; ++i) tot += wsum[i];
-  const float inv = rsqrtf(tot / a.hidden + a.eps);
-#pragma unroll
-  for (int j = 0; j < kGroups; ++j) {
-    const int n = 4 * (tid + kOProjOneThreads * j);
-    if (n < a.hidden) {
-      uint2 o;
-      o.x = f32_to_bf16(z[j].x * inv * bf16_to_f32(static_cast<uint16_t>(w[j].x))) |
-            (static_cast<uint32_t>(f32_to_bf16(z[j].y * inv * bf16_to_f32(static_cast<uint16_t>(w[j].x >> 16)))) << 16);
-      o.y = f32_to_bf16(z[j].z * inv * bf16_to_f32(static_cast<uint16_t>(w[j].y))) |
-            (static_cast<uint32_t>(f32_to_bf16(z[j].w * inv * bf16_to_f32(static_cast<uint16_t>(w[j].y >> 16)))) << 16);
-      *reinterpret_cast<uint2*>(a.normed_out + base + n) = o;
-    }
-  }
-}
-
-
-// The same for tile-major partials (the 256-sequence GEMV form), two
-// sequences per workgroup: sequences 2i and 2i + 1 own the two 64-byte
-// halves of every 128-byte line of their partials, so this workgroup reads
-// whole lines that no other workgroup touches, where one workgroup per
-// sequence fetched each line twice, on two CUs (256 x 5120: 10.6 against
-// 14.4 us in kernel traces).  In each group of eight threads, thread q
-// takes sequence 2i + q / 4 and features 4 (q % 4) .. +3 of a 16-feature
-// piece.
-template <int kSlots>
-__global__ __launch_bounds__(kOProjOneThreads) void oproj_pair_kernel(OProjArgs a) {
-  constexpr int kGroups = 2 * kOProjOneFeatures / 4;  // groups of four features per thread, at most
-  constexpr int kPieces = kOProjOneThreads / 8;       // 16-feature pieces per round
-  __shared__ float wsum[2][kOProjOneThreads / 64];
-  const int tid = threadIdx.x;
-  const int q = tid & 7;
-  const int sq = q >> 2;
-  const int b = 2 * blockIdx.x + sq;
-  const bool live = b < a.batch;  // an odd batch: the last workgroup has one sequence
-  const int64_t base = static_cast<int64_t>(b) * a.hidden;
-  float4 z[kGroups];
-  uint2 w[kGroups];
-  float ss = 0.f;
-#pragma unroll
-  for (int j = 0; j < kGroups; ++j) {
-    const int n = 16 * ((tid >> 3) + kPieces * j) + 4 * (q & 3);
-    z[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-    w[j] = make_uint2(0u, 0u);
-    if (live && n < a.hidden) {
-      w[j] = *reinterpret_cast<const uint2*>(a.norm_w + n);
-      const uint2 r = *reinterpret_cast<const uint2*>(a.residual + base + n);
-      const float4 y = gemv_rows4<kSlots>(a.part, a.plan, a.batch, b, n);
-      z[j] = make_float4(y.x + bf16_to_f32(static_cast<uint16_t>(r.x)), y.y + bf16_to_f32(static_cast<uint16_t>(r.x >> 16)),
-                         y.z + bf16_to_f32(static_cast<uint16_t>(r.y)), y.w + bf16_to_f32(static_cast<uint16_t>(r.y >> 16)));
-      ss += z[j].x * z[j].x + z[j].y * z[j].y + z[j].z * z[j].z + z[j].w * z[j].w;
-      uint2 o;
-      o.x = f32_to_bf16(z[j].x) | (static_cast<uint32_t>(f32_to_bf16(z[j].y)) << 16);
-      o.y = f32_to_bf16(z[j].z) | (static_cast<uint32_t>(f32_to_bf16(z[j].w)) << 16);
-      *reinterpret_cast<uint2*>(a.residual_out + base + n) = o;
-    }
-  }
-  // per-sequence sums: the lanes of one sequence share bit 2 of the lane id
-  ss += __shfl_xor(ss, 32);
-  ss += __shfl_xor(ss, 16);
-  ss += __shfl_xor(ss, 8);
-  ss += __shfl_xor(ss, 2);
-  ss += __shfl_xor(ss, 1);
-  if ((tid & 63) == 0) wsum[0][tid >> 6] = ss;
-  if ((tid & 63) == 4) wsum[1][tid >> 6] = ss;
-  __syncthreads();
-  float tot = 0.f;
-#pragma unroll
-  for (int i = 0; i < kOProjOneThreads / 64; ++i) tot += wsum[sq][i];
-  const float inv = rsqrtf(tot / a.hidden + a.eps);
-#pragma unroll
-  for (int j = 0; j < kGroups; ++j) {
-    const int n = 16 * ((tid >> 3) + kPieces * j) + 4 * (q & 3);
-    if (live && n < a.hidden) {
-      uint2 o;
-      o.x = f32_to_bf16(z[j].x * inv * bf16_to_f32(static_cast<uint16_t>(w[j].x))) |
-            (static_cast<uint32_t>(f32_to_bf16(z[j].y * inv * bf16_to_f32(static_cast<uint16_t>(w[j].x >> 16)))) << 16);
-      o.y = f32_to_bf16(z[j].z * inv * bf16_to_f32(static_cast<uint16_t>(w[j].y))) |
-            (static_cast<uint32_t>(f32_to_bf16(z[j].w * inv * bf16_to_f32(static_cast<uint16_t>(w[j].y >> 16)))) << 16);
-      *reinterpret_cast<uint2*>(a.normed_out + base + n) = o;
-    }
-  }
-}
-
 }  // namespace
-
-// Instantiations of the epilogues by the plan's partial slots per group.
-template <int kSlots>
-hipError_t launch_oproj_residual(const OProjArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((oproj_residual_kernel<kSlots>), dim3(a.batch * oproj_chunks(a.hidden)), dim3(kOProjChunk), 0,
-                     st, a);
-  return hipGetLastError();
-}
-
-template <int D>
-hipError_t launch_prelude(const PreludeArgs& a, hipStream_t st) {
-  const dim3 grid(a.batch * (a.hq + 2 * a.hkv));
-  if (a.plan.slots <= 4)
-    hipLaunchKernelGGL((prelude_epilogue<D, 4>), grid, dim3(64), 0, st, a);
-  else if (a.plan.slots <= 8)
-    hipLaunchKernelGGL((prelude_epilogue<D, 8>), grid, dim3(64), 0, st, a);
-  else if (a.plan.slots <= 12)
-    hipLaunchKernelGGL((prelude_epilogue<D, 12>), grid, dim3(64), 0, st, a);
-  else
-    hipLaunchKernelGGL((prelude_epilogue<D, kGemvMaxSlots>), grid, dim3(64), 0, st, a);
-  return hipGetLastError();
-}
-
-template <int kSlots>
-hipError_t launch_oproj_one(const OProjArgs& a, hipStream_t st) {
-  if (a.plan.seq_major)
-    hipLaunchKernelGGL((oproj_one_kernel<kSlots>), dim3(a.batch), dim3(kOProjOneThreads), 0, st, a);
-  else  // tile-major partials (the 256-sequence GEMV form): two sequences per workgroup
-    hipLaunchKernelGGL((oproj_pair_kernel<kSlots>), dim3((a.batch + 1) / 2), dim3(kOProjOneThreads), 0, st, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_oproj_epilogue(const OProjArgs& a, hipStream_t st) {
-  // PDA_OPROJ_ONE=0 in the environment keeps the two passes at every batch (for measurement)
-  static const bool one_ok = [] {
-    const char* e = std::getenv("PDA_OPROJ_ONE");
-    return !(e && e[0] == '0');
-  }();
-  // (the one-kernel form moves four bf16 features at a time: 8-byte aligned rows)
-  const bool aligned8 = ((reinterpret_cast<uintptr_t>(a.residual) | reinterpret_cast<uintptr_t>(a.norm_w) |
-                          reinterpret_cast<uintptr_t>(a.residual_out) | reinterpret_cast<uintptr_t>(a.normed_out)) &
-                         7) == 0;
-  if (one_ok && aligned8 && oproj_one_kernel(a.batch, a.hidden)) {
-    return a.plan.slots <= 4   ? launch_oproj_one<4>(a, st)
-           : a.plan.slots <= 8  ? launch_oproj_one<8>(a, st)
-           : a.plan.slots <= 12 ? launch_oproj_one<12>(a, st)
-                                : launch_oproj_one<kGemvMaxSlots>(a, st);
-  }
-  const dim3 grid(a.batch * oproj_chunks(a.hidden));
-  const hipError_t e = a.plan.slots <= 4   ? launch_oproj_residual<4>(a, st)
-                       : a.plan.slots <= 8  ? launch_oproj_residual<8>(a, st)
-                       : a.plan.slots <= 12 ? launch_oproj_residual<12>(a, st)
-                                            : launch_oproj_residual<kGemvMaxSlots>(a, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(oproj_norm_kernel, grid, dim3(kOProjChunk), 0, st, a);
-  return hipGetLastError();
-}
 
 hipError_t launch_pack(const uint16_t* w, uint16_t* wp, int n, int k, hipStream_t st) {
   const int64_t chunks = static_cast<int64_t>(n) * k / 8;
@@ -1009,158 +846,190 @@ hipError_t launch_pack(const uint16_t* w, uint16_t* wp, int n, int k, hipStream_
   return hipGetLastError();
 }
 
-GemvPlan plan_gemv(int batch, int n, int k, int num_cus, bool seq_major) {
-  GemvPlan p;
+// The instantiated forms of rows_kernel (launch_rows_any must list the same).
+// Row tiles x column tiles are bounded by a wave's registers (its
+// accumulators, two blocks of weights, a step's operands): 32 tiles with one
+// wave per SIMD, 16 with two.
+struct RowsForm {
+  int rt, bt, waves, kb;
+  bool wide;
+};
+static constexpr RowsForm kRowsForms[] = {
+    {1, 1, 8, 2, false}, {2, 1, 8, 2, false}, {3, 1, 8, 2, false}, {4, 1, 8, 2, false},
+    {1, 2, 8, 2, false}, {2, 2, 8, 2, false}, {3, 2, 8, 2, false}, {4, 2, 8, 2, false},
+    {1, 4, 8, 4, false}, {2, 4, 8, 4, false}, {3, 4, 8, 2, false}, {4, 4, 8, 2, false},
+    {6, 4, 4, 2, true},  {8, 4, 4, 1, false}, {4, 6, 4, 2, true},  {4, 8, 4, 2, true}};
+
+// The form, and the k splits, with the least estimated time (us).  Per round
+// of workgroups the estimate joins, as the root of the squares, a
+// workgroup's bytes at the rate a CU takes them in (70 KB/us: its loads
+// return in order, so activations from L2 queue behind weights from memory)
+// and the round's weights at 8 TB/s, and adds 1 us per round for its ramp;
+// the sum over the waves takes 0.015 us per KB of accumulators, an epilogue
+// in a kernel of its own 1.5 us and 1 us per MB of partials it reads.
+// Launch costs, the same for all, are left out.  Over 143 shapes (six
+// preludes and five output projections at 13 batches from 1 to 256; 2329
+// timed forms) the form chosen is on average 1.3% slower than the fastest
+// one, at most 11%.
+static RowsPlan search_rows(int batch, int n, int k, int num_cus, bool fusable, int max_splits) {
   const int nbt = (batch + 15) / 16;
   const int tiles = n / kTileRows;
-  // Several row tiles per unit share each x fragment: as many as there are
-  // 16-column batch tiles.  Within one batch tile of more than 4 sequences,
-  // four, when every workgroup still gets at least kGemvGroupedUnits units
-  // (x rows past the batch read as zeros with no traffic, so a few
-  // sequences gain nothing; at 8 and 16 sequences four tiles per unit ran
-  // 7% and 24% faster on 8192 x 8192 and 15% on 3072 x 5120, but 20% slower
-  // on 3072 x 3072, where the larger partials of too few units per
-  // workgroup cost more than the x reads saved).
-  p.kt_count = k / kTileK;
-  p.xlds = false;
-  p.group = 1;
-  // batches of more than 16: the thin-GEMM form when the row tiles split
-  // into groups of kXWaves (PDA_GEMV_THIN=0 in the environment selects
-  // gemv_kernel instead, for measurement, up to 64 sequences; above that
-  // only the thin-GEMM form exists, and the callers check the rows)
-  static const bool thin_ok = [] {
-    const char* e = std::getenv("PDA_GEMV_THIN");
-    return !(e && e[0] == '0');
-  }();
-  if ((thin_ok || nbt > 4) && nbt > 1 && tiles % kXWaves == 0) {
-    p.xlds = true;
-    p.group = kXWaves;
-    p.units = static_cast<int64_t>(tiles / kXWaves) * p.kt_count;
-    int64_t grid = static_cast<int64_t>(num_cus) * kXBlocksPerCu;
-    const int64_t most = (p.units + kGemvMinTiles - 1) / kGemvMinTiles;  // >= kGemvMinTiles tiles per wave
-    if (grid > most) grid = most;
-    const int64_t cap = static_cast<int64_t>(kGemvMaxSlots - 1) * (tiles / kXWaves);
-    if (grid > cap) grid = cap;
-    if (grid < 1) grid = 1;
-    p.grid = static_cast<int>(grid);
-    p.blocks = grid;
-    p.slots = static_cast<int>((static_cast<int64_t>(p.kt_count) * p.blocks + p.units - 1) / p.units + 1);
-    // above 8 column tiles (gemv_thin_kernel) the partials stay tile-major:
-    // sequence-major stores there made the 256-sequence GEMVs 15-20% slower
-    p.seq_major = seq_major && nbt <= 8;
-    return p;
+  const int bt_small = nbt <= 2 ? nbt : 4;  // up to 64 sequences: one column group
+  RowsPlan best{};
+  double best_us = 0;
+  for (const RowsForm& f : kRowsForms) {
+    if (nbt <= 4 ? f.bt != bt_small : f.bt < 4) continue;
+    const int cols = (nbt + f.bt - 1) / f.bt;
+    if (nbt > 4 && cols < 2) continue;  // (the forms for one column group stop at four tiles)
+    if (nbt > 4 && f.rt == 1) continue;
+    const int rows = (tiles + f.rt - 1) / f.rt;
+    for (int fused = 0; fused <= 1; ++fused) {
+      if (fused && (!fusable || f.rt % 2)) continue;
+      for (int splits = 1; splits <= (fused ? 1 : max_splits); ++splits) {
+        const int64_t wgs = static_cast<int64_t>(rows) * cols * splits;
+        if (splits > 1 && wgs > num_cus) break;  // splitting only fills a round
+        // Exactly one workgroup of several row tiles per CU, up to 16
+        // sequences, measured 10% above its estimate (4 x 8192 -> 8192: 28.8
+        // us with two row tiles on 256 CUs, 26.3 with three on 171, 26.4 with
+        // two workgroups of one on each)
+        if (!fused && f.bt == 1 && f.rt > 1 && wgs == num_cus) continue;
+        const double wk = 2.0 * k / splits / 1e3;  // KB per row
+        const double x_rows = batch < 16 * f.bt ? batch : 16 * f.bt;
+        const double in_us = (16 * f.rt + x_rows) * wk / 70.0;
+        const double w_us = 16.0 * f.rt * wk / cols / 8e3;  // per workgroup in the round
+        auto round_us = [&](double m) { return std::sqrt(in_us * in_us + m * w_us * m * w_us) + 1.0; };
+        const int64_t full = wgs / num_cus, rest = wgs % num_cus;
+        double us = full * round_us(num_cus) + (rest ? round_us(static_cast<double>(rest)) : 0.0) +
+                    0.015 * f.rt * f.bt * f.waves;
+        if (!fused) us += 1.5 + 4e-6 * splits * batch * static_cast<double>(n);
+        if (best.grid && us >= best_us) continue;
+        best_us = us;
+        best.rt = f.rt, best.bt = f.bt, best.waves = f.waves, best.kb = f.kb, best.wide = f.wide;
+        best.fused = fused != 0;
+        best.row_groups = rows;
+        best.col_groups = cols;
+        best.splits = splits;
+        best.split_grid = cols > 1 ? (rows + 7) / 8 * 8 * cols : rows;
+        best.grid = best.split_grid * splits;
+        best.ss_parts = rows_ss_parts(f.rt, f.bt, f.waves, f.wide);
+      }
+    }
   }
-  if (nbt > 1 && tiles % nbt == 0) {
-    p.group = nbt;
-  } else if (nbt == 1 && batch > 4 && tiles % 4 == 0 &&
-             static_cast<int64_t>(tiles / 4) * p.kt_count >=
-                 static_cast<int64_t>(kGemvGroupedUnits) * num_cus * gemv_blocks_per_cu(1, 4)) {
-    p.group = 4;
-  }
-  p.units = static_cast<int64_t>(tiles / p.group) * p.kt_count;
-  // workgroups resident per CU: the kernel's registers (its launch bounds)
-  // and the LDS of the cross-wave reduction (4 waves x group x column tiles
-  // x 1 KB) both limit it; a grid larger than what is resident would run in
-  // two rounds
-  const int lds = kGemvWaves * p.group * nbt * 1024;
-  int per_cu = (160 * 1024) / lds;
-  const int regs = gemv_blocks_per_cu(nbt, p.group);
-  per_cu = per_cu < regs ? per_cu : regs;
-  int64_t grid = static_cast<int64_t>(num_cus) * per_cu;
-  const int64_t most = (p.units + static_cast<int64_t>(kGemvWaves) * kGemvMinTiles - 1) /
-                       (static_cast<int64_t>(kGemvWaves) * kGemvMinTiles);
-  if (grid > most) grid = most;
-  // at most kGemvMaxSlots workgroups per row group: blocks <= (kGemvMaxSlots - 1) * groups
-  const int64_t cap = static_cast<int64_t>(kGemvMaxSlots - 1) * (tiles / p.group);
-  if (grid > cap) grid = cap;
-  if (grid < 1) grid = 1;
-  p.grid = static_cast<int>(grid);
-  p.blocks = grid;
-  // workgroups touching one row group: its kt_count units span at most this many ranges
-  p.slots = static_cast<int>((static_cast<int64_t>(p.kt_count) * p.blocks + p.units - 1) / p.units + 1);
-  p.seq_major = seq_major;
-  return p;
+  return best;
 }
 
-int64_t gemv_partial_floats(const GemvPlan& p, int batch, int n) {
-  return static_cast<int64_t>(n / kTileRows) * p.slots * batch * kTileRows;  // groups * group tiles = n / 16
+// The search takes about 1 us, a tenth of a small call; a decode loop asks for
+// the same few sizes, so each thread keeps its last ones (a plan follows from
+// the sizes alone).
+RowsPlan plan_rows(int batch, int n, int k, int num_cus, bool fusable, int max_splits) {
+  struct Entry {
+    int batch, n, k, num_cus, max_splits;
+    bool fusable;
+    RowsPlan plan;
+  };
+  constexpr unsigned kEntries = 16;
+  static thread_local Entry kept[kEntries];
+  Entry& e = kept[(static_cast<unsigned>(batch) * 7u + static_cast<unsigned>(n) / 16u + static_cast<unsigned>(k) / 32u * 3u +
+                   (fusable ? 5u : 0u)) % kEntries];
+  if (e.batch != batch || e.n != n || e.k != k || e.num_cus != num_cus || e.max_splits != max_splits ||
+      e.fusable != fusable || !e.plan.grid)
+    e = Entry{batch, n, k, num_cus, max_splits, fusable, search_rows(batch, n, k, num_cus, fusable, max_splits)};
+  return e.plan;
 }
 
-template <int kNBT>
-hipError_t launch_xlds(const GemvArgs& a, hipStream_t st) {
-  constexpr int lds = gemv_xlds_lds_bytes(kNBT);
-  // the dynamic-LDS limit is raised once per device (bit = device ordinal)
-  static std::atomic<uint64_t> attr_set{0};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  const uint64_t bit = dev < 64 ? uint64_t{1} << dev : 0;
-  if (!bit || !(attr_set.load() & bit)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemv_xlds_kernel<kNBT>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    attr_set.fetch_or(bit);
+namespace {
+
+template <int RT, int BT, int W, int DX, int KB, bool kWide, bool kShared, class Epilogue>
+hipError_t launch_rows_as(const RowsArgs& a, const RowsPlan& p, const Epilogue& e, hipStream_t st) {
+  constexpr int lds = rows_lds_bytes(RT, BT, W, DX);
+  auto* fn = &rows_kernel<RT, BT, W, DX, KB, kWide, kShared, Epilogue>;
+  if constexpr (lds > 64 * 1024) {
+    // the dynamic-LDS limit is raised once per device (bit = device ordinal)
+    static std::atomic<uint64_t> attr_set{0};
+    int dev = 0;
+    hipError_t err = hipGetDevice(&dev);
+    if (err != hipSuccess) return err;
+    const uint64_t bit = dev < 64 ? uint64_t{1} << dev : 0;
+    if (!bit || !(attr_set.load() & bit)) {
+      err = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      if (err != hipSuccess) return err;
+      attr_set.fetch_or(bit);
+    }
   }
-  hipLaunchKernelGGL((gemv_xlds_kernel<kNBT>), dim3(a.plan.grid), dim3(kXWaves * 64), lds, st, a.x, a.wp, a.part,
-                     a.batch, a.n, a.k, a.plan.slots, a.plan.seq_major ? 1 : 0);
+  hipLaunchKernelGGL(fn, dim3(p.grid), dim3(W * 64), lds, st, a, e);
   return hipGetLastError();
 }
 
-template <int kNBT, int kW, int kR, int kC, int kD>
-hipError_t launch_thin(const GemvArgs& a, hipStream_t st) {
-  constexpr int lds = (kD + 1) * kC * kNBT * 1024;
-  static std::atomic<uint64_t> attr_set{0};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  const uint64_t bit = dev < 64 ? uint64_t{1} << dev : 0;
-  if (!bit || !(attr_set.load() & bit)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemv_thin_kernel<kNBT, kW, kR, kC, kD>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    attr_set.fetch_or(bit);
+template <class Epilogue>
+hipError_t launch_rows_any(RowsArgs a, const RowsPlan& p, const Epilogue& e, hipStream_t st) {
+  a.row_groups = p.row_groups;
+  a.col_groups = p.col_groups;
+  a.splits = p.splits;
+  a.split_grid = p.split_grid;
+  constexpr bool kPairs = std::is_same<Epilogue, PreludeArgs>::value;
+#define PDA_ROWS(RT, BT, W, DX, KB, WD, SH) \
+  if (p.rt == RT && p.bt == BT && p.waves == W && p.wide == WD && p.kb == KB && (p.col_groups > 1) == SH) \
+    return launch_rows_as<RT, BT, W, DX, KB, WD, SH, Epilogue>(a, p, e, st);
+  if constexpr (!kPairs) {
+    PDA_ROWS(1, 1, 8, 2, 2, false, false)
+    PDA_ROWS(3, 1, 8, 2, 2, false, false)
+    PDA_ROWS(1, 2, 8, 2, 2, false, false)
+    PDA_ROWS(3, 2, 8, 2, 2, false, false)
+    PDA_ROWS(1, 4, 8, 2, 4, false, false)
+    PDA_ROWS(3, 4, 8, 2, 2, false, false)
+    PDA_ROWS(3, 4, 8, 2, 2, false, true)
   }
-  hipLaunchKernelGGL((gemv_thin_kernel<kNBT, kW, kR, kC, kD>), dim3(a.plan.grid), dim3(kW * 64), lds, st, a.x, a.wp,
-                     a.part, a.batch, a.n, a.k, a.plan.slots);
+  PDA_ROWS(2, 1, 8, 2, 2, false, false)
+  PDA_ROWS(4, 1, 8, 2, 2, false, false)
+  PDA_ROWS(2, 2, 8, 2, 2, false, false)
+  PDA_ROWS(4, 2, 8, 2, 2, false, false)
+  PDA_ROWS(2, 4, 8, 2, 4, false, false)
+  PDA_ROWS(4, 4, 8, 2, 2, false, false)
+  PDA_ROWS(6, 4, 4, 2, 2, true, false)
+  PDA_ROWS(8, 4, 4, 1, 1, false, false)
+  PDA_ROWS(2, 4, 8, 2, 4, false, true)
+  PDA_ROWS(4, 4, 8, 2, 2, false, true)
+  PDA_ROWS(6, 4, 4, 2, 2, true, true)
+  PDA_ROWS(4, 6, 4, 2, 2, true, true)
+  PDA_ROWS(4, 8, 4, 2, 2, true, true)
+  PDA_ROWS(8, 4, 4, 1, 1, false, true)
+#undef PDA_ROWS
+  return hipErrorInvalidValue;
+}
+
+template <int D>
+hipError_t launch_prelude(const PreludeArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL((prelude_epilogue<D>), dim3(a.batch * (a.hq + 2 * a.hkv)), dim3(64), 0, st, a);
   return hipGetLastError();
 }
 
-hipError_t launch_gemv(const GemvArgs& a, hipStream_t st) {
-  const dim3 grid(a.plan.grid);
-  const int nbt = (a.batch + 15) / 16;
-  const int sl = a.plan.slots;
-  // Above 128 sequences the LDS-copy form with two row tiles per wave: on
-  // the 256-sequence prelude (5120 -> 7168) it ran 40.8 against 46.2 us for
-  // gemv_xlds_kernel<16>, on the o_proj (5120 -> 5120) 31.4 against 33.0.
-  // Up to 128 sequences gemv_xlds_kernel is the faster form (batch 64,
-  // 4096 -> 6144: 15.1 us against 17.1 for the LDS-copy form at its best
-  // depth).
-  if (a.plan.xlds) {
-    if (nbt == 2) return launch_xlds<2>(a, st);
-    if (nbt == 3) return launch_xlds<3>(a, st);
-    if (nbt == 4) return launch_xlds<4>(a, st);
-    if (nbt <= 8) return launch_xlds<8>(a, st);  // column tiles past the batch read zeros
-    return launch_thin<16, 4, 2, 1, 4>(a, st);
-  }
-  if (nbt > 4) return hipErrorInvalidValue;  // above 64 sequences only the thin-GEMM form
-  const bool grouped = a.plan.group > 1;
-#define PDA_GEMV(NBT, R) \
-  hipLaunchKernelGGL((gemv_kernel<NBT, R>), grid, dim3(kGemvThreads), 0, st, a.x, a.wp, a.part, a.batch, a.n, a.k, sl, \
-                     a.plan.seq_major ? 1 : 0)
-  switch (nbt) {
-    case 1: if (grouped) PDA_GEMV(1, 4); else PDA_GEMV(1, 1); break;
-    case 2: if (grouped) PDA_GEMV(2, 2); else PDA_GEMV(2, 1); break;
-    case 3: if (grouped) PDA_GEMV(3, 3); else PDA_GEMV(3, 1); break;
-    default: if (grouped) PDA_GEMV(4, 4); else PDA_GEMV(4, 1); break;
-  }
-#undef PDA_GEMV
-  return hipGetLastError();
+}  // namespace
+
+hipError_t launch_rows(const RowsArgs& a, const RowsPlan& p, hipStream_t st) {
+  return launch_rows_any(a, p, NoEpilogue{}, st);
+}
+hipError_t launch_rows_prelude(const RowsArgs& a, const RowsPlan& p, const PreludeArgs& e, hipStream_t st) {
+  return launch_rows_any(a, p, e, st);
+}
+hipError_t launch_rows_residual(const RowsArgs& a, const RowsPlan& p, const OProjArgs& o, hipStream_t st) {
+  return launch_rows_any(a, p, o, st);
 }
 
 hipError_t launch_prelude_epilogue(const PreludeArgs& a, hipStream_t st) {
   if (a.d == 64) return launch_prelude<64>(a, st);
   if (a.d == 128) return launch_prelude<128>(a, st);
   return launch_prelude<256>(a, st);
+}
+
+hipError_t launch_oproj_sum(const OProjArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(oproj_sum_kernel, dim3(a.batch), dim3(kSumThreads), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_oproj_norm(const OProjArgs& a, hipStream_t st) {
+  const int chunks = (a.hidden + kNormFeatures - 1) / kNormFeatures;
+  hipLaunchKernelGGL(oproj_norm_kernel, dim3(a.batch * chunks), dim3(kNormThreads), 0, st, a);
+  return hipGetLastError();
 }
 
 }  // namespace pda
