@@ -1,10 +1,16 @@
-"""ctypes binding of libpda.so (argument marshalling only).
+"""Binding of libpda.so (argument marshalling only).
 
 Every step of paged decode attention runs in the HIP kernels of the library;
 this module only checks tensor metadata, extracts device pointers and sizes
 and forwards them, with torch's current HIP stream, to the C ABI declared in
 include/pda.h.  There is no fallback: if the library cannot be loaded, every
 call raises.
+
+The calls of a decode step are marshalled by ``_lib/pda_native.so``
+(csrc/pda_native.cpp), which takes the plain accepted case -- one prelude call
+costs ~4 us of host time that way, its two launches included, against ~15 us
+through the checks below and ctypes -- and declines everything else; what it
+declines goes through the checks below, which name what is wrong.
 """
 from __future__ import annotations
 
@@ -16,6 +22,7 @@ from typing import Optional, Tuple
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "_lib", "libpda.so")
+NATIVE_PATH = os.path.join(_PKG, "_lib", "pda_native.so")
 HEADER = os.path.join(os.path.dirname(_PKG), "include", "pda.h")
 
 PDA_OK = 0
@@ -23,6 +30,13 @@ ERRORS = {1: "PDA_ERR_NULL", 2: "PDA_ERR_SHAPE", 3: "PDA_ERR_UNSUPPORTED", 4: "P
           5: "PDA_ERR_ALIGN", 6: "PDA_ERR_HIP", 7: "PDA_ERR_DTYPE", 8: "PDA_ERR_LAYOUT"}
 
 _lib: Optional[ctypes.CDLL] = None
+_nat = None        # the native marshalling module, once loaded
+_DECLINED = -1     # its answer where the Python checks are to be run
+
+# entry points the native module calls
+_NATIVE_CALLS = ("paged_decode_attention_ext", "paged_decode_attention_noalloc", "paged_decode_attention_append",
+                 "pda_kv_append_n", "pda_attention_prelude", "pda_attention_prelude_append",
+                 "pda_o_proj_residual_norm")
 
 
 class PdaError(RuntimeError):
@@ -153,6 +167,26 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
         _declare(lib)
         _lib = lib
     return _lib
+
+
+def _load_native():
+    """The native marshalling module, set up with the loaded library."""
+    global _nat
+    if _nat is None:
+        import importlib.util
+
+        import torch  # first: the module's symbols are torch's
+        lib = load()
+        if not os.path.exists(NATIVE_PATH):
+            raise RuntimeError(f"native marshalling not built: {NATIVE_PATH} is missing "
+                               "(run python -m paper_2606_07665_amd.build)")
+        spec = importlib.util.spec_from_file_location("pda_native", NATIVE_PATH)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        mod.init({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_CALLS},
+                 torch._C._cuda_getCurrentRawStream)
+        _nat = mod
+    return _nat
 
 
 def declared_symbols(header: str = HEADER):
@@ -318,6 +352,12 @@ def paged_decode_attention(q, k_cache, v_cache, block_table, context_lens, out, 
     block_table: int32 [B, maxp]; context_lens: int32 [B]; all contiguous on
     one GPU.  Launches on ``stream`` (default: torch's current stream).
     """
+    rc = (_nat or _load_native()).attention(q, k_cache, v_cache, block_table, context_lens, out, scale, None, stream,
+                                            False)
+    if rc == PDA_OK:
+        return out
+    if rc != _DECLINED:
+        _check(rc)
     b, hq, d, n, p, hkv, dev = _check_attention_args(q, k_cache, v_cache, block_table, context_lens, out)
     _check(raw_call(q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), block_table.data_ptr(),
                     context_lens.data_ptr(), out.data_ptr(), b, hq, hkv, d, p, n, block_table.shape[1],
@@ -329,6 +369,12 @@ def paged_decode_attention_noalloc(q, k_cache, v_cache, block_table, context_len
     """:func:`paged_decode_attention` through the entry point that allocates
     nothing: its partials go to the library's fixed per-device scratch
     (NOALLOC_SCRATCH_BYTES).  Calls on one device must not overlap in time."""
+    rc = (_nat or _load_native()).attention(q, k_cache, v_cache, block_table, context_lens, out, scale, None, stream,
+                                            True)
+    if rc == PDA_OK:
+        return out
+    if rc != _DECLINED:
+        _check(rc)
     b, hq, d, n, p, hkv, dev = _check_attention_args(q, k_cache, v_cache, block_table, context_lens, out)
     _check(load().paged_decode_attention_noalloc(
         q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), block_table.data_ptr(), context_lens.data_ptr(),
@@ -365,6 +411,13 @@ def paged_decode_attention_ext(q, k_cache, v_cache, block_table, context_lens, o
     = the last W keys up to the query's position.  Other arguments as for
     :func:`paged_decode_attention`.
     """
+    rc = (_nat or _load_native()).attention(q, k_cache, v_cache, block_table, context_lens, out, scale,
+                                            False if window is None else window, stream,
+                                            False)
+    if rc == PDA_OK:
+        return out
+    if rc != _DECLINED:
+        _check(rc)
     import torch
     sz = _validate([("q", q, torch.bfloat16, "B T Hq D"), *_cache_specs(k_cache, v_cache, block_table, context_lens),
                     ("out", out, torch.bfloat16, "B T Hq D")])
@@ -378,6 +431,11 @@ def paged_decode_attention_ext(q, k_cache, v_cache, block_table, context_lens, o
 def kv_append(k_new, v_new, k_cache, v_cache, block_table, context_lens, stream=None):
     """Scatter each sequence's new key/value ([B, Hkv, D] bf16) into its page
     slot at position context_lens[b] - 1 (the length counts the new token)."""
+    rc = (_nat or _load_native()).kv_append(k_new, v_new, k_cache, v_cache, block_table, context_lens, False, stream)
+    if rc == PDA_OK:
+        return
+    if rc != _DECLINED:
+        _check(rc)
     import torch
     sz = _validate([("k_new", k_new, torch.bfloat16, "B Hkv D"), ("v_new", v_new, torch.bfloat16, "B Hkv D"),
                     *_cache_specs(k_cache, v_cache, block_table, context_lens)])
@@ -389,6 +447,11 @@ def kv_append(k_new, v_new, k_cache, v_cache, block_table, context_lens, stream=
 def kv_append_n(k_new, v_new, k_cache, v_cache, block_table, context_lens, stream=None):
     """Scatter T new tokens per sequence ([B, T, Hkv, D] bf16) to positions
     context_lens[b] - T + j (the lengths count all of them)."""
+    rc = (_nat or _load_native()).kv_append(k_new, v_new, k_cache, v_cache, block_table, context_lens, True, stream)
+    if rc == PDA_OK:
+        return
+    if rc != _DECLINED:
+        _check(rc)
     import torch
     sz = _validate([("k_new", k_new, torch.bfloat16, "B T Hkv D"), ("v_new", v_new, torch.bfloat16, "B T Hkv D"),
                     *_cache_specs(k_cache, v_cache, block_table, context_lens)])
@@ -400,6 +463,12 @@ def kv_append_n(k_new, v_new, k_cache, v_cache, block_table, context_lens, strea
 def paged_decode_attention_append(q, k_new, v_new, k_cache, v_cache, block_table, context_lens, out, scale,
                                   stream=None):
     """kv_append then paged_decode_attention on the same stream."""
+    rc = (_nat or _load_native()).attention_append(q, k_new, v_new, k_cache, v_cache, block_table, context_lens, out,
+                                                   scale, stream)
+    if rc == PDA_OK:
+        return out
+    if rc != _DECLINED:
+        _check(rc)
     import torch
     sz = _validate([("q", q, torch.bfloat16, "B Hq D"), ("k_new", k_new, torch.bfloat16, "B Hkv D"),
                     ("v_new", v_new, torch.bfloat16, "B Hkv D"),
@@ -448,6 +517,12 @@ def attention_prelude(x, w_packed, context_lens, q_out, k_out, v_out, *, num_q_h
     token (x: bf16 [B, H]; w_packed [(Hq + 2 Hkv) D, H] from
     :func:`pack_weights`; context_lens int32 [B]; q_out [B, Hq, D]; k_out,
     v_out [B, Hkv, D]; bias [(Hq + 2 Hkv) D]; q_norm, k_norm [D])."""
+    rc = (_nat or _load_native()).prelude(x, w_packed, context_lens, q_out, k_out, v_out, None, num_q_heads, num_kv_heads,
+                                          head_dim, rope_theta, rotary_dim, interleaved, bias, q_norm, k_norm, eps, stream)
+    if rc == PDA_OK:
+        return
+    if rc != _DECLINED:
+        _check(rc)
     import torch
     known = dict(Hq=int(num_q_heads), Hkv=int(num_kv_heads), D=int(head_dim),
                  N=(int(num_q_heads) + 2 * int(num_kv_heads)) * int(head_dim))
@@ -468,6 +543,14 @@ def attention_prelude_append(x, w_packed, context_lens, q_out, k_cache, v_cache,
     page slot at position context_lens[b] - 1 (caches [N, P, Hkv, D],
     block_table int32 [B, maxp]; other arguments as for
     :func:`attention_prelude`)."""
+    rc = (_nat or _load_native()).prelude(x, w_packed, context_lens, q_out, k_cache, v_cache,
+                                          False if block_table is None else block_table, num_q_heads,
+                                          num_kv_heads, head_dim, rope_theta, rotary_dim, interleaved, bias, q_norm, k_norm,
+                                          eps, stream)
+    if rc == PDA_OK:
+        return
+    if rc != _DECLINED:
+        _check(rc)
     import torch
     known = dict(Hq=int(num_q_heads), Hkv=int(num_kv_heads), D=int(head_dim),
                  N=(int(num_q_heads) + 2 * int(num_kv_heads)) * int(head_dim))
@@ -552,6 +635,11 @@ def o_proj_residual_norm(attn, w_packed, residual, norm_w, residual_out, normed_
     """z = W_o attn + residual -> residual_out (bf16); RMSNorm(z) * norm_w ->
     normed_out.  attn [B, K], w_packed [H, K] from :func:`pack_weights`,
     residual / outputs [B, H], norm_w [H]; residual_out may be residual."""
+    rc = (_nat or _load_native()).o_proj(attn, w_packed, residual, norm_w, residual_out, normed_out, eps, stream)
+    if rc == PDA_OK:
+        return
+    if rc != _DECLINED:
+        _check(rc)
     import torch
     bf = torch.bfloat16
     sz = _validate([("attn", attn, bf, "B K"), ("w_packed", w_packed, bf, "H K"), ("residual", residual, bf, "B H"),
