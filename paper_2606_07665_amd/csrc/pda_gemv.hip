@@ -864,7 +864,9 @@ static constexpr RowsForm kRowsForms[] = {
 // of workgroups the estimate joins, as the root of the squares, a
 // workgroup's bytes at the rate a CU takes them in (70 KB/us: its loads
 // return in order, so activations from L2 queue behind weights from memory)
-// and the round's weights at 8 TB/s, and adds 1 us per round for its ramp;
+// and the round's weights at 8 TB/s, and adds 1 us per round for its ramp
+// (once for workgroups of one tile, which share a CU: 3 x 8192 -> 10240 29.8
+// us in 1280 of them, 30.7 in 214 of three row tiles);
 // the sum over the waves takes 0.015 us per KB of accumulators, an epilogue
 // in a kernel of its own 1.5 us and 1 us per MB of partials it reads.
 // Launch costs, the same for all, are left out.  Over 143 shapes (six
@@ -887,7 +889,10 @@ static RowsPlan search_rows(int batch, int n, int k, int num_cus, bool fusable, 
       if (fused && (!fusable || f.rt % 2)) continue;
       for (int splits = 1; splits <= (fused ? 1 : max_splits); ++splits) {
         const int64_t wgs = static_cast<int64_t>(rows) * cols * splits;
-        if (splits > 1 && wgs > num_cus) break;  // splitting only fills a round
+        // workgroups of one row tile and one column tile: several reside on a
+        // CU and their loads overlap, so rounds run together
+        const bool small = f.rt == 1 && f.bt == 1;
+        if (splits > 1 && wgs > num_cus && !small) break;  // splitting only fills a round
         // Exactly one workgroup of several row tiles per CU, up to 16
         // sequences, measured 10% above its estimate (4 x 8192 -> 8192: 28.8
         // us with two row tiles on 256 CUs, 26.3 with three on 171, 26.4 with
@@ -897,10 +902,15 @@ static RowsPlan search_rows(int batch, int n, int k, int num_cus, bool fusable, 
         const double x_rows = batch < 16 * f.bt ? batch : 16 * f.bt;
         const double in_us = (16 * f.rt + x_rows) * wk / 70.0;
         const double w_us = 16.0 * f.rt * wk / cols / 8e3;  // per workgroup in the round
-        auto round_us = [&](double m) { return std::sqrt(in_us * in_us + m * w_us * m * w_us) + 1.0; };
         const int64_t full = wgs / num_cus, rest = wgs % num_cus;
-        double us = full * round_us(num_cus) + (rest ? round_us(static_cast<double>(rest)) : 0.0) +
-                    0.015 * f.rt * f.bt * f.waves;
+        double us = 0.015 * f.rt * f.bt * f.waves;
+        if (small) {
+          const double rounds = static_cast<double>(full + (rest ? 1 : 0)), w_all = static_cast<double>(wgs) * w_us;
+          us += std::sqrt(rounds * in_us * rounds * in_us + w_all * w_all) + 1.0;
+        } else {
+          auto round_us = [&](double m) { return std::sqrt(in_us * in_us + m * w_us * m * w_us) + 1.0; };
+          us += full * round_us(num_cus) + (rest ? round_us(static_cast<double>(rest)) : 0.0);
+        }
         if (!fused) us += 1.5 + 4e-6 * splits * batch * static_cast<double>(n);
         if (best.grid && us >= best_us) continue;
         best_us = us;
