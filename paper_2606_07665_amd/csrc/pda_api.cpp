@@ -195,10 +195,10 @@ int heads_per_group(int hkv, int max_waves) {
 // Workgroups: one wave per kv head of a group of hgs, times step phases up
 // to max_waves(d) waves (8; 4 at D = 256); as many workgroups as fill the
 // device (blocks_per_cu per CU), but none with fewer than min_steps 32-token
-// steps per wave at the largest context the page table allows.  Partial
+// steps per wave when every sequence has steps_seq steps.  Partial
 // slots: one per (workgroup, sequence piece), at most grid + batch * kv-head
 // groups, each holding `cols` (query token, head) rows per kv head.
-Plan plan_for(int hgs, int32_t batch, int32_t hkv, int32_t d, int32_t p, int32_t maxp, int num_cus, int cols,
+Plan plan_for(int hgs, int32_t batch, int32_t hkv, int32_t d, int64_t steps_seq, int num_cus, int cols,
               int min_steps) {
   Plan pl;
   const int max_waves = pda::max_waves(d);
@@ -207,8 +207,7 @@ Plan plan_for(int hgs, int32_t batch, int32_t hkv, int32_t d, int32_t p, int32_t
   const int phases = max_waves / pl.hgs;
   pl.waves = pl.hgs * phases;
   const int64_t ngroups = hkv / pl.hgs;
-  const int64_t max_ctx = static_cast<int64_t>(maxp) * p;
-  const int64_t steps_max = static_cast<int64_t>(batch) * ngroups * ((max_ctx + pda::kStep - 1) / pda::kStep);
+  const int64_t steps_max = static_cast<int64_t>(batch) * ngroups * steps_seq;
   const int64_t per_block = static_cast<int64_t>(min_steps) * phases;
   int64_t blocks = (steps_max + per_block - 1) / per_block;
   const int64_t target = static_cast<int64_t>(num_cus) * blocks_per_cu();
@@ -225,6 +224,15 @@ Plan plan_for(int hgs, int32_t batch, int32_t hkv, int32_t d, int32_t p, int32_t
   return pl;
 }
 
+// Most 32-token steps a sequence can have: what the page table holds, or with
+// a sliding window the steps that window + num_queries - 1 tokens touch.
+int64_t most_steps(int32_t p, int32_t maxp, int num_queries, int window) {
+  const int64_t table = (static_cast<int64_t>(maxp) * p + pda::kStep - 1) / pda::kStep;
+  if (window <= 0) return table;
+  const int64_t seen = (static_cast<int64_t>(window) + num_queries - 1 + pda::kStep - 1) / pda::kStep + 1;
+  return std::min(table, seen);
+}
+
 // The fixed split of a latency-bound call with the kv-head grouping and
 // step count of `base`: every (sequence, kv-head group) is cut into the same
 // number of chunks of whole 32-token steps, as many as the stream-K plan
@@ -235,15 +243,12 @@ Plan plan_for(int hgs, int32_t batch, int32_t hkv, int32_t d, int32_t p, int32_t
 // a plan with grid 0 where it does not apply: more pairs than half the
 // device's workgroups (the stream-K split balances those better).  One
 // partial slot per workgroup.
-Plan plan_fixed(const Plan& base, int32_t batch, int32_t hkv, int32_t d, int32_t p, int32_t maxp, int num_cus,
-                int cols) {
+Plan plan_fixed(const Plan& base, int32_t batch, int32_t hkv, int32_t d, int64_t steps_seq, int num_cus, int cols) {
   Plan pl = base;
   pl.grid = 0;
   const int phases = pl.waves / pl.hgs;
   const int64_t seqs = static_cast<int64_t>(batch) * (hkv / pl.hgs);
   const int64_t target = static_cast<int64_t>(num_cus) * blocks_per_cu();
-  const int64_t max_ctx = static_cast<int64_t>(maxp) * p;
-  const int64_t steps_seq = (max_ctx + pda::kStep - 1) / pda::kStep;
   const int64_t per_block = static_cast<int64_t>(pl.min_steps) * phases;
   if (base.grid < 1 || 2 * seqs > target) return pl;
   int64_t chunks = 1;
@@ -266,7 +271,7 @@ Plan plan_fixed(const Plan& base, int32_t batch, int32_t hkv, int32_t d, int32_t
   return pl;
 }
 
-// The plan of a call.  The default reads all kv heads of a group of up to 8
+// The split plan of a call.  The default reads all kv heads of a group of up to 8
 // together (the faster access order for long streams) and merges split
 // sequences in a separate kernel.  With PDA_OPT_FUSED_MERGE = 1, a grid of
 // several workgroups with little partial data per sequence merges inside
@@ -286,7 +291,7 @@ constexpr int64_t kSmallCallBytes = int64_t{128} << 20;
 constexpr int64_t kSmallCallPieces = 32;
 constexpr int kDefaultMinSteps = 2;
 
-Plan make_plan(int32_t batch, int32_t hkv, int32_t d, int32_t p, int32_t maxp, int num_cus, int cols) {
+Plan make_split_plan(int32_t batch, int32_t hkv, int32_t d, int64_t steps_seq, int num_cus, int cols) {
   const int cap = kv_group_cap();
   const int ms_opt = min_steps_option();
   // A split piece leaves a partial of cols x head_dim fp32 per kv head it
@@ -296,7 +301,7 @@ Plan make_plan(int32_t batch, int32_t hkv, int32_t d, int32_t p, int32_t maxp, i
   // columns or fewer, run slower with 4).
   const int dflt_most = cols > 8 ? std::min(4, pda::max_waves(d)) : pda::max_waves(d);
   const int most = cap > 0 && cap < pda::max_waves(d) ? cap : dflt_most;
-  Plan dflt = plan_for(heads_per_group(hkv, most), batch, hkv, d, p, maxp, num_cus, cols,
+  Plan dflt = plan_for(heads_per_group(hkv, most), batch, hkv, d, steps_seq, num_cus, cols,
                        ms_opt > 0 ? ms_opt : kDefaultMinSteps);
   // Small calls (each 32-token step's K and V is a few KB; the whole call
   // is a chain of latencies):
@@ -316,16 +321,16 @@ Plan make_plan(int32_t batch, int32_t hkv, int32_t d, int32_t p, int32_t maxp, i
   //    first K/V loads leave ~2 us earlier and the merge needs no prefix
   //    (1 x 4096 tokens, 32:8 heads, cold K/V: attention kernel 14.8 ->
   //    11.4 us by events, 16.7 -> 11.9 us per call replayed from a graph).
-  const int64_t kv_bytes = static_cast<int64_t>(batch) * maxp * p * hkv * d * 4;
+  const int64_t kv_bytes = static_cast<int64_t>(batch) * steps_seq * pda::kStep * hkv * d * 4;
   const bool small = kv_bytes <= kSmallCallBytes;
   if (small) {
     if (ms_opt == 0 && dflt.grid > 1 && dflt.grid < static_cast<int64_t>(num_cus) * blocks_per_cu())
-      dflt = plan_for(dflt.hgs, batch, hkv, d, p, maxp, num_cus, cols, 1);
+      dflt = plan_for(dflt.hgs, batch, hkv, d, steps_seq, num_cus, cols, 1);
     if (cap == 0) {
       for (int h = dflt.hgs; h >= 1; --h) {
         if (hkv % h) continue;
         if (h == 1 || static_cast<int64_t>(dflt.grid) * h <= kSmallCallPieces * batch * hkv) {
-          if (h != dflt.hgs) dflt = plan_for(h, batch, hkv, d, p, maxp, num_cus, cols, dflt.min_steps);
+          if (h != dflt.hgs) dflt = plan_for(h, batch, hkv, d, steps_seq, num_cus, cols, dflt.min_steps);
           break;
         }
       }
@@ -334,14 +339,14 @@ Plan make_plan(int32_t batch, int32_t hkv, int32_t d, int32_t p, int32_t maxp, i
   // (the vector-ALU variant, a measurement aid, keeps the merge kernel)
   if (dflt.grid == 1 || !fused_merge() || compute_path() != 0) {
     if (small && fixed_split() && compute_path() == 0) {
-      const Plan f = plan_fixed(dflt, batch, hkv, d, p, maxp, num_cus, cols);
+      const Plan f = plan_fixed(dflt, batch, hkv, d, steps_seq, num_cus, cols);
       if (f.grid > 0) return f;
     }
     return dflt;
   }
   // a latency-bound call keeps the fixed split, merged in the kernel
   if (small && fixed_split()) {
-    Plan f = plan_fixed(dflt, batch, hkv, d, p, maxp, num_cus, cols);
+    Plan f = plan_fixed(dflt, batch, hkv, d, steps_seq, num_cus, cols);
     if (f.grid > 1 && f.chunks > 1 && f.grid <= pda::kMaxFusedGrid) {
       f.fused = true;
       return f;
@@ -354,7 +359,7 @@ Plan make_plan(int32_t batch, int32_t hkv, int32_t d, int32_t p, int32_t maxp, i
   }
   for (int h = dflt.hgs; h >= 1; --h) {
     if (hkv % h) continue;
-    Plan c = plan_for(h, batch, hkv, d, p, maxp, num_cus, cols, dflt.min_steps);
+    Plan c = plan_for(h, batch, hkv, d, steps_seq, num_cus, cols, dflt.min_steps);
     const int64_t most_bytes = static_cast<int64_t>(c.grid) * h * cols * d * 4;
     if (c.grid > 1 && c.grid <= pda::kMaxFusedGrid && most_bytes <= pda::kFusedMergeBytes &&
         c.bytes < (int64_t{1} << 31)) {
@@ -365,18 +370,62 @@ Plan make_plan(int32_t batch, int32_t hkv, int32_t d, int32_t p, int32_t maxp, i
   return dflt;
 }
 
+// Whole sequences, one workgroup per (sequence, kv-head group) and nothing to
+// merge, for calls whose sequences are all short: the fewest kv heads a
+// workgroup that give every pair a CU of its own.  It is the fixed split with
+// one chunk per pair.  Taken where even the longest sequence the table (or
+// the window) allows ends before a split plan's merge would: a workgroup
+// takes about 6 us + its K/V bytes at 42 KB/us, a split plan at least 9 us
+// (its merge kernel and boundary are 4 of them), and 13 where the pairs are
+// too many for the fixed split, since its workgroups then take several
+// sequences one after another.  Replayed from a graph, split -> whole: 16 x
+// 160 tokens, 32:8 heads 10.2 -> 7.9 us; 64 x 64 10.7 -> 7.7; 256 x 64 18.6
+// -> 12.3; 32:2 heads, 128 x 64 27.5 -> 7.6, 256 x 256 40 -> 14.  With longer
+// sequences a few long ones among short ones would cost more whole.
+Plan plan_whole(const Plan& split, int32_t batch, int32_t hkv, int32_t d, int64_t steps_seq, int num_cus) {
+  Plan pl = split;
+  pl.grid = 0;
+  const int max_waves = pda::max_waves(d);
+  const bool streamed = 2 * static_cast<int64_t>(batch) * (hkv / heads_per_group(hkv, max_waves)) > num_cus;
+  const int64_t most_kb = streamed ? 300 : 150;
+  for (int h = 1; h <= max_waves; ++h) {
+    if (hkv % h || static_cast<int64_t>(batch) * (hkv / h) > num_cus) continue;
+    if (steps_seq * pda::kStep * h * d * 4 > most_kb * 1024) break;
+    pl.hgs = h;
+    pl.waves = h * (max_waves / h);
+    pl.grid = static_cast<int>(static_cast<int64_t>(batch) * (hkv / h));
+    pl.chunks = 1;
+    pl.chunk_steps = static_cast<int>(steps_seq);
+    pl.fused = false;
+    return pl;  // (the split plan's workspace, unused, is kept: the same calls fit the same scratch)
+  }
+  return pl;
+}
+
+// The plan of a call: the split plan, or whole sequences where that is
+// faster, unless an option asks for a particular split.
+Plan make_plan(int32_t batch, int32_t hkv, int32_t d, int64_t steps_seq, int num_cus, int cols) {
+  const Plan split = make_split_plan(batch, hkv, d, steps_seq, num_cus, cols);
+  if (split.chunks == 1 || !fixed_split() || compute_path() != 0 || fused_merge() || kv_group_cap() ||
+      min_steps_option() || blocks_per_cu() != 1)
+    return split;
+  const Plan whole = plan_whole(split, batch, hkv, d, steps_seq, num_cus);
+  return whole.grid > 0 ? whole : split;
+}
+
 // Workspace that any call of this shape may need: the largest plan over
 // every kv-head group size and step count make_plan can pick, at 16 columns
 // per kv head.
 int64_t reserve_bytes(int32_t batch, int32_t hkv, int32_t d, int32_t p, int32_t maxp, int num_cus) {
+  const int64_t steps_seq = most_steps(p, maxp, 1, 0);  // a windowed call has no more
   const int ms_opt = min_steps_option();
   int64_t most = 0;
   for (int ms : {ms_opt > 0 ? ms_opt : kDefaultMinSteps, ms_opt > 0 ? ms_opt : 1})
     for (int h = 1; h <= pda::max_waves(d); ++h)
       if (hkv % h == 0) {
-        const Plan pl = plan_for(h, batch, hkv, d, p, maxp, num_cus, pda::kMaxCols, ms);
+        const Plan pl = plan_for(h, batch, hkv, d, steps_seq, num_cus, pda::kMaxCols, ms);
         most = std::max(most, pl.bytes);
-        most = std::max(most, plan_fixed(pl, batch, hkv, d, p, maxp, num_cus, pda::kMaxCols).bytes);
+        most = std::max(most, plan_fixed(pl, batch, hkv, d, steps_seq, num_cus, pda::kMaxCols).bytes);
       }
   return most;
 }
@@ -807,7 +856,8 @@ int attention_call(const void* q, const void* k_cache, const void* v_cache, cons
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
   int cus = 0;
   if ((rc = device_cus(dev, &cus))) return rc;
-  const Plan pl = make_plan(batch, num_kv_heads, head_dim, page_size, max_pages_per_seq, cus, cols);
+  const Plan pl = make_plan(batch, num_kv_heads, head_dim,
+                            most_steps(page_size, max_pages_per_seq, num_queries, window), cus, cols);
   if (pda::attn_lds_bytes(head_dim, batch, pl.waves, valu_cols > 0) > static_cast<size_t>(pda::kMaxLdsBytes))
     return fail(PDA_ERR_UNSUPPORTED, "batch %d needs more LDS than a workgroup has", batch);
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -895,7 +945,7 @@ int pda_plan(int32_t batch, int32_t num_q_heads, int32_t num_kv_heads, int32_t h
   int rc = check_attention(batch, num_q_heads, num_kv_heads, head_dim, page_size, max_pages_per_seq);
   if (rc) return rc;
   if (num_cus <= 0) return fail(PDA_ERR_SHAPE, "num_cus must be positive");
-  Plan pl = make_plan(batch, num_kv_heads, head_dim, page_size, max_pages_per_seq, num_cus,
+  Plan pl = make_plan(batch, num_kv_heads, head_dim, most_steps(page_size, max_pages_per_seq, 1, 0), num_cus,
                       num_q_heads / num_kv_heads);
   *grid_blocks = batch ? pl.grid : 0;
   *waves = batch ? pl.grid * pl.waves : 0;
