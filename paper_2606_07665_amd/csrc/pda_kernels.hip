@@ -11,7 +11,7 @@
 //  * Work split (stream-K over the context).  The flattened space of
 //    (sequence b, kv-head group, 32-token step) is cut into equal contiguous
 //    ranges, one per workgroup, so every workgroup moves the same amount of
-//    KV whatever the length mix.  A workgroup has one wave per kv head of the
+//    KV whatever the length mix (short sequences count for a little more).  A workgroup has one wave per kv head of the
 //    group (up to 8), times phases that interleave steps when there are fewer
 //    than 8 kv heads: all heads of a token range are read together, so a page
 //    (token rows of 2*D*Hkv bytes) is consumed in one sweep.  On MI355X this
@@ -370,9 +370,24 @@ __global__ __launch_bounds__(64 * max_waves(D), 1) void attn_kernel(
   const int tid = threadIdx.x;
   const int page = 1 << page_shift;
   const int max_ctx = maxp << page_shift;
+  // What a sequence counts for in the stream-K ranges: its steps, and for a
+  // short one `phases` steps more, ahead of its own, for the latency of
+  // taking up another piece (page ids, then K, then V, then the exchange of
+  // the phases: ~5 us that nothing overlaps).  Counted by steps alone, a
+  // workgroup of a ragged batch got 8 or more short sequences in a row and
+  // the others waited for it.  A step of eight heads (one phase, D = 128) is
+  // 128 KB, ~5 us of a CU's share of memory by itself, and covers it: none
+  // there.  Batches of 31 to 256 sequences (Zipf and two-length mixes, 20 to
+  // 1000 MB), geometric mean of the time against steps alone: 8:1 heads,
+  // D = 128 0.67, 32:2 0.78, 24:4 0.89, 8:1 at D = 64 0.74, 12:4 at D = 256
+  // 0.95 (one phase), 8:1 at D = 256 0.76; with it 32:8 at D = 128 would be
+  // 1.01 and 40:40 1.04.  Half as much gives 0.76, 0.84, 0.89, 0.82, 0.98,
+  // 0.83; limits of 4 and 16 steps per phase are within 1%.
+  const int extra = (phases > 1 || D == 256) ? phases : 0;
+  auto extent = [&](int steps) { return steps + (steps > 0 && steps < 8 * phases ? extra : 0); };
 
   if constexpr (!kFixed) {
-    // ---- per-block prefix over the batch of 32-token steps per sequence ----
+    // ---- per-block prefix over the batch of the extent of each sequence ----
     // Each thread sums a run of sequences; a shuffle scan inside each wave and
     // one exchange of wave totals through LDS make the prefix with two
     // barriers (a tree over the workgroup took ~2 us of barriers).
@@ -389,7 +404,7 @@ __global__ __launch_bounds__(64 * max_waves(D), 1) void attn_kernel(
       const int lo = tid * per;
       const int hi = min(batch, lo + per);
       int sum = 0;
-      for (int b = lo; b < hi; ++b) sum += seq_steps(S::kLensInLds ? lens_s[b] : clamp_len(lens[b], max_ctx), nq, window);
+      for (int b = lo; b < hi; ++b) sum += extent(seq_steps(S::kLensInLds ? lens_s[b] : clamp_len(lens[b], max_ctx), nq, window));
       int incl = sum;  // inclusive prefix within the wave
   #pragma unroll
       for (int off = 1; off < 64; off <<= 1) {
@@ -403,7 +418,7 @@ __global__ __launch_bounds__(64 * max_waves(D), 1) void attn_kernel(
       int run = before + incl - sum;
       for (int b = lo; b < hi; ++b) {
         pref[b] = run;
-        run += seq_steps(S::kLensInLds ? lens_s[b] : clamp_len(lens[b], max_ctx), nq, window);
+        run += extent(seq_steps(S::kLensInLds ? lens_s[b] : clamp_len(lens[b], max_ctx), nq, window));
       }
       if (tid == nthreads - 1) pref[batch] = before + incl;
       __syncthreads();
@@ -533,7 +548,7 @@ __global__ __launch_bounds__(64 * max_waves(D), 1) void attn_kernel(
   const int64_t xend = kFixed ? (fx_nb - fx_s0 < chunk_steps ? fx_nb - fx_s0 : chunk_steps)
                               : (static_cast<int64_t>(blk + 1) * total) / beff;
 
-  // sequence containing step x: largest b with pref[b] * ngroups <= x
+  // sequence containing position x: largest b with pref[b] * ngroups <= x
   int b = fx_b;
   if constexpr (!kFixed) {
     const int y = static_cast<int>(x / ngroups);
@@ -572,6 +587,10 @@ __global__ __launch_bounds__(64 * max_waves(D), 1) void attn_kernel(
     const int npages = (L + page - 1) >> page_shift;
     const int lo_seq = uniform(seq_start(L, nq, window));
     const int sb = lo_seq / kStep;                  // first step of the sequence
+    // the piece's steps [t0, t1): its range without the extent ahead of the
+    // sequence's steps (a piece within that has none: partial of weight 0)
+    const int lead = kFixed ? 0 : nb - ((L + kStep - 1) / kStep - sb);
+    const int t0 = max(s0 - lead, 0), t1 = max(s1 - lead, 0);
     // keys [lo_c, hi_c) of this lane's column; steps that cross a bound mask
     const int hi_c = L - nq + 1 + qj;
     const int lo_c = window > 0 ? max(0, hi_c - window) : 0;
@@ -631,8 +650,8 @@ __global__ __launch_bounds__(64 * max_waves(D), 1) void attn_kernel(
     // A step's loads are issued only once the previous step's have all
     // arrived: one step in flight per wave while the previous one computes
     // streams ~1% faster on MI355X than letting two steps overlap.
-    const int sw = s0 + ph;  // this wave's first step; it takes sw, sw + phases, ...
-    const int nsteps = sw < s1 ? (s1 - sw + phases - 1) / phases : 0;
+    const int sw = t0 + ph;  // this wave's first step; it takes sw, sw + phases, ...
+    const int nsteps = sw < t1 ? (t1 - sw + phases - 1) / phases : 0;
     auto step_of = [&](int k) {  // k-th step of this wave (absolute), clamped to its last one
       k = k < nsteps ? k : nsteps - 1;
       return sb + sw + k * phases;
@@ -1007,7 +1026,7 @@ __global__ __launch_bounds__(64 * max_waves(D), 1) void attn_kernel(
       // barrier, so each wave passes the same number of them.  (The
       // small-page path runs ~3% slower with it: its waves already wait on
       // their page-id shuffles at every issue.)
-      const int nmin = kLanePages ? 0 : (s1 - s0) / phases;
+      const int nmin = kLanePages ? 0 : (t1 - t0) / phases;
       // (Small pages read their page ids with vector loads, which the wait
       // for all vector loads would also wait for: they are issued after it.)
       for (; k + 2 < nsteps; k += 2) {
