@@ -871,8 +871,8 @@ static constexpr RowsForm kRowsForms[] = {
 // in a kernel of its own 1.5 us and 1 us per MB of partials it reads.
 // Launch costs, the same for all, are left out.  Over 143 shapes (six
 // preludes and five output projections at 13 batches from 1 to 256; 2329
-// timed forms) the form chosen is on average 1.3% slower than the fastest
-// one, at most 11%.
+// timed forms) the form chosen is on average 1.2% slower than the fastest
+// one, at most 8%.
 static RowsPlan search_rows(int batch, int n, int k, int num_cus, bool fusable, int max_splits) {
   const int nbt = (batch + 15) / 16;
   const int tiles = n / kTileRows;
