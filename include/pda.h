@@ -408,7 +408,10 @@ int32_t pda_version(void);
  *                          the merge finds the pieces from the lengths).
  *                          Where the stream-K plan would take a single
  *                          workgroup, every pair is one chunk: whole
- *                          sequences on separate workgroups, no merge.
+ *                          sequences on separate workgroups, no merge; so
+ *                          are calls whose sequences are all short (by the
+ *                          page table or the window).  With a window the
+ *                          steps it can touch count, not the table's.
  *                          0: every call is split stream-K over the actual
  *                          lengths.  Both are deterministic for a fixed
  *                          plan; they round differently.
