@@ -535,7 +535,7 @@ int pda_attention_prelude_append(const void* x, const void* w_packed, const void
                                  const pda_prelude_dims* dims, void* stream);
 
 /* [library interface] Grow the (current device, stream) workspace for a
-   prelude of these dims. */
+   prelude of these dims, and of every smaller batch. */
 int pda_prelude_workspace_reserve(const pda_prelude_dims* dims, void* stream);
 
 /*
@@ -565,8 +565,30 @@ int pda_o_proj_residual_norm(const void* attn, const void* w_packed, const void*
                              void* residual_out, void* normed_out, int32_t batch, int32_t in_features,
                              int32_t hidden, float eps, void* stream);
 /* [library interface] Grow the (current device, stream) workspace for an
-   o_proj call of this shape. */
+   o_proj call of this shape, and of every smaller batch. */
 int pda_o_proj_workspace_reserve(int32_t batch, int32_t in_features, int32_t hidden, void* stream);
+
+/*
+ * pda_prelude_plan, pda_o_proj_plan [library interface] -- host-only dry runs
+ * of the planner of the projection y = x W^T in a prelude (qk_norm: with norm
+ * weights) and in an output projection, as pda_plan for attention.  No HIP
+ * call.  (A prelude whose outputs lie over x or the weights runs unfused,
+ * whatever the plan says.)  Errors as for the calls' arguments; batch 0 gives
+ * all zeros.
+ */
+typedef struct {
+  int32_t row_tiles, col_tiles; /* per workgroup: 16 rows of W, 16 sequences each  */
+  int32_t wide;                 /* 1: 32 x 32 x 16 matrix instructions             */
+  int32_t col_groups;           /* workgroups that share the same rows             */
+  int32_t k_splits;             /* parts of the k range                            */
+  int32_t fused;                /* 1: the prelude's epilogue runs in the kernel    */
+  int32_t workgroups;           /* with work                                       */
+  int32_t ss_parts;             /* o_proj, unsplit: sums of z^2 per 16 features    */
+  int64_t workspace_bytes;      /* that the call asks for: enough for every smaller
+                                   batch of the same sizes                         */
+} pda_projection;
+int pda_prelude_plan(const pda_prelude_dims* dims, int32_t qk_norm, int32_t num_cus, pda_projection* out);
+int pda_o_proj_plan(int32_t batch, int32_t in_features, int32_t hidden, int32_t num_cus, pda_projection* out);
 
 #ifdef __cplusplus
 }

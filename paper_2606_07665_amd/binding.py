@@ -52,6 +52,12 @@ class PreludeDims(ctypes.Structure):
                 ("interleaved", ctypes.c_int32), ("rope_theta", ctypes.c_float), ("eps", ctypes.c_float)]
 
 
+class Projection(ctypes.Structure):
+    """pda_projection of include/pda.h."""
+    _fields_ = [(name, ctypes.c_int32) for name in ("row_tiles", "col_tiles", "wide", "col_groups", "k_splits", "fused",
+                                                    "workgroups", "ss_parts")] + [("workspace_bytes", ctypes.c_int64)]
+
+
 DTYPE_BF16, DTYPE_F16, DTYPE_F32, DTYPE_I32, DTYPE_I64 = range(5)  # pda_dtype
 MAX_DIMS = 4
 
@@ -119,6 +125,10 @@ def _declare(lib: ctypes.CDLL) -> None:
     lib.pda_o_proj_residual_norm.restype = ctypes.c_int
     lib.pda_o_proj_workspace_reserve.argtypes = [i32, i32, i32, vp]
     lib.pda_o_proj_workspace_reserve.restype = ctypes.c_int
+    lib.pda_prelude_plan.argtypes = [dims_p, i32, i32, ctypes.POINTER(Projection)]
+    lib.pda_prelude_plan.restype = ctypes.c_int
+    lib.pda_o_proj_plan.argtypes = [i32, i32, i32, i32, ctypes.POINTER(Projection)]
+    lib.pda_o_proj_plan.restype = ctypes.c_int
     lib.pda_kv_append.argtypes = [vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, vp]
     lib.pda_kv_append_n.argtypes = [vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, vp]
     lib.pda_kv_append_n.restype = ctypes.c_int
@@ -569,6 +579,13 @@ def prelude_workspace_reserve(dims: PreludeDims, stream=None) -> None:
     _check(load().pda_prelude_workspace_reserve(ctypes.byref(dims), _stream_ptr(stream)))
 
 
+def prelude_plan(dims: PreludeDims, qk_norm: bool = False, num_cus: int = 256) -> Projection:
+    """How the projection of a prelude of these dims is split (no HIP call)."""
+    p = Projection()
+    _check(load().pda_prelude_plan(ctypes.byref(dims), int(bool(qk_norm)), num_cus, ctypes.byref(p)))
+    return p
+
+
 def plan(batch, hq, hkv, d, page_size, max_pages, num_cus=256) -> Tuple[int, int, int]:
     """(grid blocks, waves, workspace bytes) the split planner picks."""
     g, w, ws = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int64()
@@ -652,6 +669,13 @@ def o_proj_residual_norm(attn, w_packed, residual, norm_w, residual_out, normed_
 
 def o_proj_workspace_reserve(batch, in_features, hidden, stream=None) -> None:
     _check(load().pda_o_proj_workspace_reserve(batch, in_features, hidden, _stream_ptr(stream)))
+
+
+def o_proj_plan(batch, in_features, hidden, num_cus: int = 256) -> Projection:
+    """How an output projection of this shape is split (no HIP call)."""
+    p = Projection()
+    _check(load().pda_o_proj_plan(batch, in_features, hidden, num_cus, ctypes.byref(p)))
+    return p
 
 
 def profile_read_o_proj() -> Tuple[float, float, int]:

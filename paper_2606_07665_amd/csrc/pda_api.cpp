@@ -457,7 +457,9 @@ struct Workspace {
 std::mutex g_ws_mu;
 std::map<std::pair<int, hipStream_t>, Workspace> g_ws;
 
-int workspace_for(int dev, hipStream_t st, int64_t need, void** out) {
+// needed: false where this call does without it (it then grows for later
+// calls, and not while the stream is being captured).
+int workspace_for(int dev, hipStream_t st, int64_t need, void** out, bool needed = true) {
   std::lock_guard<std::mutex> lock(g_ws_mu);
   Workspace& ws = g_ws[{dev, st}];
   if (ws.bytes >= need) {
@@ -467,6 +469,7 @@ int workspace_for(int dev, hipStream_t st, int64_t need, void** out) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   hipError_t e = hipStreamIsCapturing(st, &cap);
   if (e != hipSuccess) return hip_fail(e, "hipStreamIsCapturing");
+  if (cap != hipStreamCaptureStatusNone && !needed) return PDA_OK;
   if (cap != hipStreamCaptureStatusNone)
     return fail(PDA_ERR_HIP, "workspace must grow to %lld bytes while the stream is being captured; "
                 "call pda_workspace_reserve before capture", static_cast<long long>(need));
@@ -708,19 +711,22 @@ bool overlaps(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
   return a && b && x < y + static_cast<uintptr_t>(b_bytes) && y < x + static_cast<uintptr_t>(a_bytes);
 }
 
+// k splits of an output projection: only where the kernel that adds them
+// holds a row of z.
+int oproj_splits(int hidden) { return hidden <= pda::kSumFeatures ? pda::kMaxRowsSplits : 1; }
+
 // Workspace of a prelude whose epilogue is a kernel of its own: the fp32
-// projection, one per k split.  (Reserved for every prelude: the reservation
-// does not know the norm weights.)
+// projection, one per k split.  Like that of the output projection it covers
+// every smaller batch of the same rows, so that a workspace grown or reserved
+// for one batch serves (also under capture) all below it, and it is asked for
+// by every prelude, whether this one's epilogue needs it or not: which do
+// depends on the batch, the norm weights and the outputs' places.
 int64_t prelude_ws_bytes(const pda_prelude_dims& d, int cus) {
-  const pda::RowsPlan plan =
-      pda::plan_rows(d.batch, static_cast<int>(prelude_rows(d)), d.hidden, cus, false, pda::kMaxRowsSplits);
-  return align256(static_cast<int64_t>(plan.splits) * d.batch * prelude_rows(d) * 4);
+  return align256(pda::rows_most_floats(d.batch, static_cast<int>(prelude_rows(d)), cus, pda::kMaxRowsSplits) * 4);
 }
 
-// k splits only where the kernel that adds them holds a row of z.
 pda::RowsPlan oproj_plan(int batch, int in_features, int hidden, int cus) {
-  return pda::plan_rows(batch, hidden, in_features, cus, false,
-                        hidden <= pda::kSumFeatures ? pda::kMaxRowsSplits : 1);
+  return pda::plan_rows(batch, hidden, in_features, cus, false, oproj_splits(hidden));
 }
 
 // o_proj workspace: z [splits, batch, hidden] in fp32, then the partial sums
@@ -729,9 +735,29 @@ int64_t oproj_ss_offset(const pda::RowsPlan& plan, int batch, int hidden) {
   return align256(static_cast<int64_t>(plan.splits) * batch * hidden * 4);
 }
 
-int64_t oproj_ws_bytes(const pda::RowsPlan& plan, int batch, int hidden) {
-  return oproj_ss_offset(plan, batch, hidden) +
-         align256(static_cast<int64_t>(batch) * (hidden / pda::kTileRows) * plan.ss_parts * 4);
+int64_t oproj_ws_bytes(int batch, int hidden, int cus) {
+  return align256(pda::rows_most_floats(batch, hidden, cus, oproj_splits(hidden)) * 4) +
+         align256(static_cast<int64_t>(batch) * (hidden / pda::kTileRows) * pda::kMaxSsParts * 4);
+}
+
+bool oproj_in_range(int32_t batch, int32_t in_features, int32_t hidden) {
+  return batch >= 0 && batch <= pda::kMaxGemvBatch && in_features > 0 && in_features % pda::kTileK == 0 && hidden > 0 &&
+         hidden % pda::kTileRows == 0 && hidden <= pda::kMaxOProjHidden &&
+         (batch <= pda::kMaxGemvBatchAnyRows || hidden % 128 == 0);
+}
+
+pda_projection projection(const pda::RowsPlan& p, int64_t workspace_bytes) {
+  pda_projection o;
+  o.row_tiles = p.rt;
+  o.col_tiles = p.bt;
+  o.wide = p.wide ? 1 : 0;
+  o.col_groups = p.col_groups;
+  o.k_splits = p.splits;
+  o.fused = p.fused ? 1 : 0;
+  o.workgroups = p.row_groups * p.col_groups * p.splits;
+  o.ss_parts = p.ss_parts;
+  o.workspace_bytes = workspace_bytes;
+  return o;
 }
 
 // Shared by both prelude entry points once their own arguments are checked.
@@ -780,7 +806,7 @@ int run_prelude(const void* x, const void* w_packed, const void* bias, const voi
   // The epilogue runs in the projection kernel where it can, unless an
   // output lies over something that kernel still reads for other outputs:
   // then the projection goes through the workspace.
-  bool fusable = pda::prelude_fusable(ep);
+  bool fusable = pda::prelude_fusable(ep.q_norm != nullptr, ep.interleaved != 0, ep.rotary_dim);
   if (fusable) {
     const int64_t kv_bytes = static_cast<int64_t>(d.batch) * d.num_kv_heads * d.head_dim * 2;
     const int64_t cache_bytes =
@@ -794,9 +820,9 @@ int run_prelude(const void* x, const void* w_packed, const void* bias, const voi
   }
   const pda::RowsPlan plan = pda::plan_rows(g.batch, g.n, g.k, cus, fusable, pda::kMaxRowsSplits);
   const bool fused = plan.fused;
+  void* ws = nullptr;
+  if ((rc = workspace_for(dev, st, prelude_ws_bytes(d, cus), &ws, !fused))) return rc;
   if (!fused) {
-    void* ws = nullptr;
-    if ((rc = workspace_for(dev, st, prelude_ws_bytes(d, cus), &ws))) return rc;
     g.y = static_cast<float*>(ws);
     ep.y = g.y;
     ep.splits = plan.splits;
@@ -1316,7 +1342,7 @@ int pda_o_proj_residual_norm(const void* attn, const void* w_packed, const void*
   hipStream_t st = static_cast<hipStream_t>(stream);
   const pda::RowsPlan plan = oproj_plan(batch, in_features, hidden, cus);
   void* ws = nullptr;
-  if ((rc = workspace_for(dev, st, oproj_ws_bytes(plan, batch, hidden), &ws))) return rc;
+  if ((rc = workspace_for(dev, st, oproj_ws_bytes(batch, hidden, cus), &ws))) return rc;
   pda::OProjArgs o;
   o.residual = static_cast<const uint16_t*>(residual);
   o.norm_w = static_cast<const uint16_t*>(norm_w);
@@ -1353,10 +1379,7 @@ int pda_o_proj_residual_norm(const void* attn, const void* w_packed, const void*
 
 int pda_o_proj_workspace_reserve(int32_t batch, int32_t in_features, int32_t hidden, void* stream) {
   g_err.clear();
-  if (batch < 0 || batch > pda::kMaxGemvBatch || in_features <= 0 || in_features % pda::kTileK ||
-      hidden <= 0 || hidden % pda::kTileRows || hidden > pda::kMaxOProjHidden ||
-      (batch > pda::kMaxGemvBatchAnyRows && hidden % 128))
-    return fail(PDA_ERR_SHAPE, "o_proj shape out of range");
+  if (!oproj_in_range(batch, in_features, hidden)) return fail(PDA_ERR_SHAPE, "o_proj shape out of range");
   if (batch == 0) return PDA_OK;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -1364,9 +1387,35 @@ int pda_o_proj_workspace_reserve(int32_t batch, int32_t in_features, int32_t hid
   int cus = 0;
   int rc = device_cus(dev, &cus);
   if (rc) return rc;
-  const pda::RowsPlan plan = oproj_plan(batch, in_features, hidden, cus);
   void* ptr = nullptr;
-  return workspace_for(dev, static_cast<hipStream_t>(stream), oproj_ws_bytes(plan, batch, hidden), &ptr);
+  return workspace_for(dev, static_cast<hipStream_t>(stream), oproj_ws_bytes(batch, hidden, cus), &ptr);
+}
+
+int pda_o_proj_plan(int32_t batch, int32_t in_features, int32_t hidden, int32_t num_cus, pda_projection* out) {
+  g_err.clear();
+  if (!out) return fail(PDA_ERR_NULL, "pda_o_proj_plan: NULL output pointer");
+  if (!oproj_in_range(batch, in_features, hidden)) return fail(PDA_ERR_SHAPE, "o_proj shape out of range");
+  if (num_cus <= 0) return fail(PDA_ERR_SHAPE, "num_cus must be positive");
+  *out = pda_projection{};
+  if (batch == 0) return PDA_OK;
+  *out = projection(oproj_plan(batch, in_features, hidden, num_cus), oproj_ws_bytes(batch, hidden, num_cus));
+  return PDA_OK;
+}
+
+int pda_prelude_plan(const pda_prelude_dims* dims, int32_t qk_norm, int32_t num_cus, pda_projection* out) {
+  g_err.clear();
+  if (!out) return fail(PDA_ERR_NULL, "pda_prelude_plan: NULL output pointer");
+  int rc = check_prelude(dims);
+  if (rc) return rc;
+  if (num_cus <= 0) return fail(PDA_ERR_SHAPE, "num_cus must be positive");
+  *out = pda_projection{};
+  if (dims->batch == 0) return PDA_OK;
+  const pda_prelude_dims& d = *dims;
+  const pda::RowsPlan plan =
+      pda::plan_rows(d.batch, static_cast<int>(prelude_rows(d)), d.hidden, num_cus,
+                     pda::prelude_fusable(qk_norm != 0, d.interleaved != 0, d.rotary_dim), pda::kMaxRowsSplits);
+  *out = projection(plan, prelude_ws_bytes(d, num_cus));
+  return PDA_OK;
 }
 
 int pda_profile_read_o_proj(double* gemv_ms, double* epilogue_ms, int64_t* calls) {

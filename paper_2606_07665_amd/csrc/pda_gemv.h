@@ -38,9 +38,14 @@ constexpr int rows_ss_parts(int rt, int bt, int waves, bool wide) {
   return (wide ? 2 : 1) * (rt * bt < waves ? 2 : 1);
 }
 
+constexpr int kMaxSsParts = 4;
+
 // fusable: the prelude epilogue may run in the kernel (the plan says whether
 // it is to).  max_splits: at most kMaxRowsSplits.
 RowsPlan plan_rows(int batch, int n, int k, int num_cus, bool fusable, int max_splits);
+// Most floats of y, all splits together, that the plan of any k and any batch
+// up to `batch` has: never less for a larger batch.
+int64_t rows_most_floats(int batch, int n, int num_cus, int max_splits);
 
 // What a prelude's epilogue does with the projection, in rows_kernel or in
 // prelude_epilogue.
@@ -69,8 +74,8 @@ struct PreludeArgs {
 // The prelude epilogues that rows_kernel can run itself: no norm over the
 // head (a workgroup holds two of its tiles), and rotation partners in the
 // two tiles of a pair (or in one, interleaved).
-inline bool prelude_fusable(const PreludeArgs& a) {
-  return !a.q_norm && (a.interleaved || a.rotary_dim % 32 == 0);
+inline bool prelude_fusable(bool qk_norm, bool interleaved, int rotary_dim) {
+  return !qk_norm && (interleaved || rotary_dim % 32 == 0);
 }
 
 constexpr int kMaxOProjHidden = 32768;

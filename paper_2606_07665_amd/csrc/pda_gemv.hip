@@ -860,6 +860,12 @@ static constexpr RowsForm kRowsForms[] = {
     {1, 4, 8, 4, false}, {2, 4, 8, 4, false}, {3, 4, 8, 2, false}, {4, 4, 8, 2, false},
     {6, 4, 4, 2, true},  {8, 4, 4, 1, false}, {4, 6, 4, 2, true},  {4, 8, 4, 2, true}};
 
+static constexpr int most_row_tiles() {
+  int most = 0;
+  for (const RowsForm& f : kRowsForms) most = f.rt > most ? f.rt : most;
+  return most;
+}
+
 // The form, and the k splits, with the least estimated time (us).  Per round
 // of workgroups the estimate joins, as the root of the squares, a
 // workgroup's bytes at the rate a CU takes them in (70 KB/us: its loads
@@ -945,6 +951,17 @@ RowsPlan plan_rows(int batch, int n, int k, int num_cus, bool fusable, int max_s
       e.fusable != fusable || !e.plan.grid)
     e = Entry{batch, n, k, num_cus, max_splits, fusable, search_rows(batch, n, k, num_cus, fusable, max_splits)};
   return e.plan;
+}
+
+// By search_rows: up to 16 sequences any number of splits; above, splits only
+// fill one round of workgroups.
+int64_t rows_most_floats(int batch, int n, int num_cus, int max_splits) {
+  constexpr int most = most_row_tiles();
+  const int rows = (n / kTileRows + most - 1) / most;
+  const int round = num_cus / rows < 1 ? 1 : num_cus / rows;
+  const int64_t few = static_cast<int64_t>(batch < 16 ? batch : 16) * max_splits;
+  const int64_t many = static_cast<int64_t>(batch) * (round < max_splits ? round : max_splits);
+  return (few > many ? few : many) * n;
 }
 
 namespace {
