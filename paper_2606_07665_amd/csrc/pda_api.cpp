@@ -413,21 +413,18 @@ Plan make_plan(int32_t batch, int32_t hkv, int32_t d, int64_t steps_seq, int num
   return whole.grid > 0 ? whole : split;
 }
 
-// Workspace that any call of this shape may need: the largest plan over
-// every kv-head group size and step count make_plan can pick, at 16 columns
-// per kv head.
-int64_t reserve_bytes(int32_t batch, int32_t hkv, int32_t d, int32_t p, int32_t maxp, int num_cus) {
-  const int64_t steps_seq = most_steps(p, maxp, 1, 0);  // a windowed call has no more
-  const int ms_opt = min_steps_option();
-  int64_t most = 0;
-  for (int ms : {ms_opt > 0 ? ms_opt : kDefaultMinSteps, ms_opt > 0 ? ms_opt : 1})
-    for (int h = 1; h <= pda::max_waves(d); ++h)
-      if (hkv % h == 0) {
-        const Plan pl = plan_for(h, batch, hkv, d, steps_seq, num_cus, pda::kMaxCols, ms);
-        most = std::max(most, pl.bytes);
-        most = std::max(most, plan_fixed(pl, batch, hkv, d, steps_seq, num_cus, pda::kMaxCols).bytes);
-      }
-  return most;
+// Workspace that any plan of these sizes may need, and of any smaller batch or
+// table, fewer columns and every window: what a call asks for, so that calls
+// of one shape that plan differently (by their windows) use one workspace,
+// also under capture.  A plan has at most one workgroup per compute unit and
+// per (sequence, kv head, step), each with one slot of up to max_waves kv
+// heads beside one per (sequence, kv-head group).
+int64_t workspace_bytes(int32_t batch, int32_t hkv, int32_t d, int32_t p, int32_t maxp, int num_cus, int cols) {
+  const int64_t target = static_cast<int64_t>(num_cus) * blocks_per_cu();
+  const int64_t pairs = static_cast<int64_t>(batch) * hkv;
+  const int64_t steps = pairs * most_steps(p, maxp, 1, 0);
+  const int64_t rows = (std::min(target * pda::max_waves(d), steps) + pairs) * cols;
+  return align256(rows * d * 4) + align256(rows * 2 * 4) + align256((batch + 1 + std::min(target, steps)) * 4);
 }
 
 int device_cus(int dev, int* cus) {
@@ -899,7 +896,8 @@ int attention_call(const void* q, const void* k_cache, const void* v_cache, cons
     if ((e = pda::noalloc_scratch(dev, &ws)) != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
     cnt = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + PDA_NOALLOC_SCRATCH_BYTES - counter_bytes);
   } else {
-    if ((rc = workspace_for(dev, st, pl.bytes, &ws))) return rc;
+    const int64_t need = workspace_bytes(batch, num_kv_heads, head_dim, page_size, max_pages_per_seq, cus, cols);
+    if ((rc = workspace_for(dev, st, need, &ws))) return rc;
     if (pl.fused && (rc = counters_for(dev, st, &cnt))) return rc;
   }
 
@@ -965,9 +963,9 @@ int32_t pda_version(void) { return PDA_VERSION; }
 
 int pda_plan(int32_t batch, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
              int32_t page_size, int32_t max_pages_per_seq, int32_t num_cus, int32_t* grid_blocks,
-             int32_t* waves, int64_t* workspace_bytes) {
+             int32_t* waves, int64_t* workspace_size) {
   g_err.clear();
-  if (!grid_blocks || !waves || !workspace_bytes) return fail(PDA_ERR_NULL, "pda_plan: NULL output pointer");
+  if (!grid_blocks || !waves || !workspace_size) return fail(PDA_ERR_NULL, "pda_plan: NULL output pointer");
   int rc = check_attention(batch, num_q_heads, num_kv_heads, head_dim, page_size, max_pages_per_seq);
   if (rc) return rc;
   if (num_cus <= 0) return fail(PDA_ERR_SHAPE, "num_cus must be positive");
@@ -975,8 +973,8 @@ int pda_plan(int32_t batch, int32_t num_q_heads, int32_t num_kv_heads, int32_t h
                       num_q_heads / num_kv_heads);
   *grid_blocks = batch ? pl.grid : 0;
   *waves = batch ? pl.grid * pl.waves : 0;
-  *workspace_bytes =
-      batch ? reserve_bytes(batch, num_kv_heads, head_dim, page_size, max_pages_per_seq, num_cus) : 0;
+  *workspace_size =
+      batch ? workspace_bytes(batch, num_kv_heads, head_dim, page_size, max_pages_per_seq, num_cus, pda::kMaxCols) : 0;
   return PDA_OK;
 }
 
@@ -993,7 +991,8 @@ int pda_workspace_reserve(int32_t batch, int32_t num_q_heads, int32_t num_kv_hea
   if ((rc = device_cus(dev, &cus))) return rc;
   // sized for the most (query token, head) columns, so any num_queries fits
   void* ptr = nullptr;
-  const int64_t need = reserve_bytes(batch, num_kv_heads, head_dim, page_size, max_pages_per_seq, cus);
+  const int64_t need =
+      workspace_bytes(batch, num_kv_heads, head_dim, page_size, max_pages_per_seq, cus, pda::kMaxCols);
   if ((rc = workspace_for(dev, static_cast<hipStream_t>(stream), need, &ptr))) return rc;
   int32_t* cnt = nullptr;
   return counters_for(dev, static_cast<hipStream_t>(stream), &cnt);
