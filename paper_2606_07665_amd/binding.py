@@ -3,14 +3,15 @@
 Every step of paged decode attention runs in the HIP kernels of the library;
 this module only checks tensor metadata, extracts device pointers and sizes
 and forwards them, with torch's current HIP stream, to the C ABI declared in
-include/pda.h.  There is no fallback: if the library cannot be loaded, every
-call raises.
+include/pda.h.  There is no fallback for the kernels: if the library cannot be
+loaded, every call raises.
 
 The calls of a decode step are marshalled by ``_lib/pda_native.so``
 (csrc/pda_native.cpp), which takes the plain accepted case -- one prelude call
 costs ~4 us of host time that way, its two launches included, against ~15 us
 through the checks below and ctypes -- and declines everything else; what it
-declines goes through the checks below, which name what is wrong.
+declines goes through the checks below, which name what is wrong, as does
+every call where that module is missing (with one warning).
 """
 from __future__ import annotations
 
@@ -179,23 +180,53 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     return _lib
 
 
+class _Declining:
+    """Stands in for the native module: every call goes through the checks."""
+
+    @staticmethod
+    def _decline(*args):
+        return _DECLINED
+
+    attention = kv_append = attention_append = prelude = o_proj = _decline
+
+
+def _built_for() -> str:
+    """What pda_native.so has to have been built for, to be used by this process."""
+    import platform
+
+    import torch
+    return f"python {platform.python_version()}, torch {torch.__version__}"
+
+
+def _import_native():
+    import importlib.util
+
+    import torch  # first: the module's symbols are torch's
+    lib = load()
+    if not os.path.exists(NATIVE_PATH):
+        raise ImportError(f"{NATIVE_PATH} is missing (run python -m paper_2606_07665_amd.build)")
+    spec = importlib.util.spec_from_file_location("pda_native", NATIVE_PATH)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    if mod.built_for != _built_for():
+        raise ImportError(f"{NATIVE_PATH} was built for {mod.built_for}; this is {_built_for()}")
+    mod.init({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_CALLS},
+             torch._C._cuda_getCurrentRawStream)
+    return mod
+
+
 def _load_native():
-    """The native marshalling module, set up with the loaded library."""
+    """The native marshalling module, set up with the loaded library; where it
+    is missing or was built for another Python or torch, the stand-in that
+    leaves every call to the checks below (the same calls, more host time)."""
     global _nat
     if _nat is None:
-        import importlib.util
-
-        import torch  # first: the module's symbols are torch's
-        lib = load()
-        if not os.path.exists(NATIVE_PATH):
-            raise RuntimeError(f"native marshalling not built: {NATIVE_PATH} is missing "
-                               "(run python -m paper_2606_07665_amd.build)")
-        spec = importlib.util.spec_from_file_location("pda_native", NATIVE_PATH)
-        mod = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(mod)
-        mod.init({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_CALLS},
-                 torch._C._cuda_getCurrentRawStream)
-        _nat = mod
+        try:
+            _nat = _import_native()
+        except ImportError as e:
+            import warnings
+            warnings.warn(f"calls are marshalled in Python: {e}", RuntimeWarning, stacklevel=3)
+            _nat = _Declining()
     return _nat
 
 

@@ -49,13 +49,16 @@ def build_library(verbose: bool = False, extra_flags=None) -> str:
 
 
 def build_native(verbose: bool = False) -> str:
-    """The CPython extension, against torch's headers (host code only)."""
+    """The CPython extension, against torch's headers (host code only); it
+    carries the versions it was built for, which the binding compares."""
     import torch
     from torch.utils import cpp_extension
+
+    from paper_2606_07665_amd.binding import _built_for
     os.makedirs(LIB_DIR, exist_ok=True)
     tmp = NATIVE_PATH + ".tmp"
     cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"]]
+           f'-DPDA_BUILT_FOR="{_built_for()}"', "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"]]
     for path in cpp_extension.include_paths():
         cmd += ["-isystem", path]
     cmd += ["-o", tmp, NATIVE_SOURCE]

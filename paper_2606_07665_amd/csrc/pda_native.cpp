@@ -352,4 +352,11 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "pda_native", "Native marshalling 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_pda_native() { return PyModule_Create(&kModule); }
+PyMODINIT_FUNC PyInit_pda_native() {
+  PyObject* m = PyModule_Create(&kModule);
+  if (m && PyModule_AddStringConstant(m, "built_for", PDA_BUILT_FOR) < 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -8,13 +8,6 @@ import workloads as W
 from paper_2606_07665_amd import binding as pda
 
 
-class _Declining:
-    """Stands in for the native module: every call goes to the Python path."""
-
-    def __getattr__(self, name):
-        return lambda *a: pda._DECLINED
-
-
 def _calls(b=3, dev="cpu"):
     """Every natively marshalled call with accepted arguments (name, args, kwargs)."""
     hq, hkv, d, p, n, m, hid, t = 4, 2, 64, 16, 4 * b, 4, 96, 2  # every sequence has pages of its own
@@ -96,12 +89,55 @@ def test_cpu_tensors_are_declined_and_refused(i):
 
 
 def test_wrong_counts_and_kinds_are_declined():
-    nat = pda._load_native()
+    nat = pda._import_native()
     for f in (nat.attention, nat.kv_append, nat.attention_append, nat.prelude, nat.o_proj):
         for n in (0, 1, 7, 8, 10, 18, 19):
             assert f(*([None] * n)) == pda._DECLINED
             assert f(*([object()] * n)) == pda._DECLINED
             assert f(*([torch.empty(2, 2, dtype=torch.bfloat16, device="meta")] * n)) == pda._DECLINED
+
+
+@pytest.mark.parametrize("kind", ["missing", "not a library", "other torch"])
+def test_without_a_native_module_the_checks_run(monkeypatch, tmp_path, kind):
+    """No pda_native.so that fits this process: a warning, and the calls go
+    through the Python checks as if it had declined them."""
+    path = tmp_path / "pda_native.so"
+    if kind == "not a library":
+        path.write_bytes(b"\x7fELF nothing")
+    if kind == "other torch":
+        path = pda.NATIVE_PATH
+        monkeypatch.setattr(pda, "_built_for", lambda: "python 3.0.0, torch 0.0.0")
+    monkeypatch.setattr(pda, "NATIVE_PATH", str(path))
+    monkeypatch.setattr(pda, "_nat", None)
+    with pytest.warns(RuntimeWarning, match="marshalled in Python"):
+        pda._load_native()
+    for name, args, kwargs in _calls():
+        with pytest.raises(ValueError, match="must be a GPU tensor"):
+            getattr(pda, name)(*args, **kwargs)
+
+
+class _Recording:
+    """The native module, with what it answered."""
+
+    def __init__(self, nat):
+        self.nat, self.answers = nat, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            self.answers.append(getattr(self.nat, name)(*args))
+            return self.answers[-1]
+        return call
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("i", range(len(NAMES)), ids=NAMES)
+def test_the_plain_call_is_taken_natively(gpu_lib, monkeypatch, i):
+    rec = _Recording(pda._import_native())
+    monkeypatch.setattr(pda, "_nat", rec)
+    name, args, kwargs = _calls(5, "cuda")[i]
+    getattr(pda, name)(*args, **kwargs)
+    torch.cuda.synchronize()
+    assert rec.answers == [pda.PDA_OK]
 
 
 @pytest.mark.gpu
@@ -111,7 +147,7 @@ def test_native_and_python_paths_agree(gpu_lib, monkeypatch, i):
     same exception, or is accepted by both."""
     got = {}
     for path in ("native", "python"):
-        monkeypatch.setattr(pda, "_nat", pda._load_native() if path == "native" else _Declining())
+        monkeypatch.setattr(pda, "_nat", pda._import_native() if path == "native" else pda._Declining())
         name, args, kwargs = _calls(5, "cuda")[i]
         getattr(pda, name)(*args, **kwargs)
         torch.cuda.synchronize()
@@ -123,7 +159,7 @@ def test_native_and_python_paths_agree(gpu_lib, monkeypatch, i):
     for what, (a, k) in _variants(args, kwargs):
         seen = []
         for path in ("native", "python"):
-            monkeypatch.setattr(pda, "_nat", pda._load_native() if path == "native" else _Declining())
+            monkeypatch.setattr(pda, "_nat", pda._import_native() if path == "native" else pda._Declining())
             seen.append(_outcome(name, a, k))
         assert seen[0] == seen[1], f"{name}, {what}: {seen}"
     torch.cuda.synchronize()
