@@ -198,7 +198,7 @@ def _built_for() -> str:
     return f"python {platform.python_version()}, torch {torch.__version__}"
 
 
-def _import_native():
+def _import_native(current_device=None):
     import importlib.util
 
     import torch  # first: the module's symbols are torch's
@@ -211,7 +211,7 @@ def _import_native():
     if mod.built_for != _built_for():
         raise ImportError(f"{NATIVE_PATH} was built for {mod.built_for}; this is {_built_for()}")
     mod.init({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_CALLS},
-             torch._C._cuda_getCurrentRawStream)
+             torch._C._cuda_getCurrentRawStream, current_device or torch._C._cuda_getDevice)
     return mod
 
 

@@ -37,6 +37,7 @@ struct Lib {
   decltype(&pda_o_proj_residual_norm) o_proj = nullptr;
 } g_lib;
 PyObject* g_raw_stream = nullptr;  // torch._C._cuda_getCurrentRawStream
+PyObject* g_device = nullptr;      // torch._C._cuda_getDevice
 
 // One call's accepted tensors: all on one GPU, contiguous.
 struct Checker {
@@ -86,11 +87,20 @@ struct Checker {
     }
     return static_cast<float>(v);
   }
-  // The raw handle of `stream`, or of torch's current stream on the device.
-  void* stream(PyObject* o) {
+  // The raw handle of `stream`, or of torch's current stream on the tensors'
+  // device.  of_current: the call takes the current device's stream instead,
+  // so tensors on another device are left to the Python path.
+  void* stream(PyObject* o, bool of_current) {
     if (!ok) return nullptr;
     PyObject* h;
     if (o == Py_None) {
+      if (of_current) {
+        PyObject* d = PyObject_CallNoArgs(g_device);
+        if (!d || PyLong_AsLong(d) != device) ok = false;
+        Py_XDECREF(d);
+        if (PyErr_Occurred()) PyErr_Clear();
+        if (!ok) return nullptr;
+      }
       PyObject* d = PyLong_FromLong(device);
       h = d ? PyObject_CallOneArg(g_raw_stream, d) : nullptr;
       Py_XDECREF(d);
@@ -171,7 +181,7 @@ PyObject* attention(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     const int32_t hkv = c.i32(kv.hkv), p = c.i32(kv.p), n = c.i32(kv.n), m = c.i32(kv.m);
     const int32_t window = ext ? c.integer(a[7]) : 0;
     const float scale = c.number(a[6]);
-    void* st = c.stream(a[8]);
+    void* st = c.stream(a[8], /*of_current=*/ext);
     if (!c.ok) return kDeclined;
     void *qp = q->data_ptr(), *kp = kv.k->data_ptr(), *vp = kv.v->data_ptr(), *op = out->data_ptr();
     int32_t *bp = ints(kv.bt), *lp = ints(kv.lens);
@@ -197,7 +207,7 @@ PyObject* kv_append(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     c.same(kn->size(several ? 2 : 1), kv.hkv);
     c.same(kn->size(several ? 3 : 2), kv.d);
     const int32_t hkv = c.i32(kv.hkv), d = c.i32(kv.d), p = c.i32(kv.p), n = c.i32(kv.n), m = c.i32(kv.m);
-    void* st = c.stream(a[7]);
+    void* st = c.stream(a[7], /*of_current=*/true);
     if (!c.ok) return kDeclined;
     void *knp = kn->data_ptr(), *vnp = vn->data_ptr(), *kp = kv.k->data_ptr(), *vp = kv.v->data_ptr();
     int32_t *bp = ints(kv.bt), *lp = ints(kv.lens);
@@ -224,7 +234,7 @@ PyObject* attention_append(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     const int32_t b = c.i32(q->size(0)), hq = c.i32(q->size(1)), d = c.i32(q->size(2));
     const int32_t hkv = c.i32(kv.hkv), p = c.i32(kv.p), n = c.i32(kv.n), m = c.i32(kv.m);
     const float scale = c.number(a[8]);
-    void* st = c.stream(a[9]);
+    void* st = c.stream(a[9], /*of_current=*/true);
     if (!c.ok) return kDeclined;
     void *qp = q->data_ptr(), *knp = kn->data_ptr(), *vnp = vn->data_ptr();
     void *kp = kv.k->data_ptr(), *vp = kv.v->data_ptr(), *op = out->data_ptr();
@@ -280,7 +290,7 @@ PyObject* prelude(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     if (qn) c.same(qn->size(0), d), c.same(kn->size(0), d);
     const int32_t pages = append ? c.i32(k->size(0)) : 0, page = append ? c.i32(k->size(1)) : 0;
     const int32_t m = append ? c.i32(bt->size(1)) : 0;
-    void* st = c.stream(a[17]);
+    void* st = c.stream(a[17], /*of_current=*/true);
     if (!c.ok) return kDeclined;
     auto ptr = [](const at::Tensor* t) -> void* { return t ? t->data_ptr() : nullptr; };
     void *xp = ptr(x), *wp = ptr(w), *bp = ptr(bias), *qnp = ptr(qn), *knp = ptr(kn), *qp = ptr(q), *kp = ptr(k), *vp = ptr(v);
@@ -309,7 +319,7 @@ PyObject* o_proj(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     c.same(res->size(1), w->size(0));
     c.same(nw->size(0), w->size(0));
     c.ok = c.ok && z->sizes() == res->sizes() && h->sizes() == res->sizes();
-    void* st = c.stream(a[7]);
+    void* st = c.stream(a[7], /*of_current=*/true);
     if (!c.ok) return kDeclined;
     void *xp = x->data_ptr(), *wp = w->data_ptr(), *rp = res->data_ptr(), *np = nw->data_ptr();
     void *zp = z->data_ptr(), *hp = h->data_ptr();
@@ -317,10 +327,11 @@ PyObject* o_proj(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   });
 }
 
-// ({name: address}, raw_stream): the loaded library's entry points
+// ({name: address}, raw_stream, device): the loaded library's entry points,
+// torch's current raw stream of a device and its current device
 PyObject* init(PyObject*, PyObject* args) {
-  PyObject *table, *raw;
-  if (!PyArg_ParseTuple(args, "O!O", &PyDict_Type, &table, &raw)) return nullptr;
+  PyObject *table, *raw, *device;
+  if (!PyArg_ParseTuple(args, "O!OO", &PyDict_Type, &table, &raw, &device)) return nullptr;
   auto set = [&](const char* name, auto& fn) {
     PyObject* v = PyDict_GetItemString(table, name);
     void* p = v ? PyLong_AsVoidPtr(v) : nullptr;
@@ -341,6 +352,9 @@ PyObject* init(PyObject*, PyObject* args) {
   Py_INCREF(raw);
   Py_XDECREF(g_raw_stream);
   g_raw_stream = raw;
+  Py_INCREF(device);
+  Py_XDECREF(g_device);
+  g_device = device;
   Py_RETURN_NONE;
 }
 

@@ -142,6 +142,23 @@ def test_the_plain_call_is_taken_natively(gpu_lib, monkeypatch, i):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("i", range(len(NAMES)), ids=NAMES)
+def test_the_stream_is_that_of_the_checks(gpu_lib, monkeypatch, i):
+    """Without a stream, the one-query attention calls take the current stream
+    of the tensors' device and the others that of the current device: with
+    another device current (here only by its answer) the native path leaves
+    those to the Python path, unless the caller names the stream."""
+    name, args, kwargs = _calls(5, "cuda")[i]
+    rec = _Recording(pda._import_native(current_device=lambda: 1))
+    monkeypatch.setattr(pda, "_nat", rec)
+    of_tensors = name in ("paged_decode_attention", "paged_decode_attention_noalloc")
+    getattr(pda, name)(*args, **kwargs)
+    getattr(pda, name)(*args, stream=torch.cuda.current_stream(), **kwargs)
+    torch.cuda.synchronize()
+    assert rec.answers == [pda.PDA_OK if of_tensors else pda._DECLINED, pda.PDA_OK]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("i", range(len(NAMES)), ids=NAMES)
 def test_native_and_python_paths_agree(gpu_lib, monkeypatch, i):
     """Accepted calls give the same bits; every changed argument gives the
     same exception, or is accepted by both."""
