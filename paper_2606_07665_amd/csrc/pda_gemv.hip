@@ -858,7 +858,7 @@ static constexpr RowsForm kRowsForms[] = {
     {1, 1, 8, 2, false}, {2, 1, 8, 2, false}, {3, 1, 8, 2, false}, {4, 1, 8, 2, false},
     {1, 2, 8, 2, false}, {2, 2, 8, 2, false}, {3, 2, 8, 2, false}, {4, 2, 8, 2, false},
     {1, 4, 8, 4, false}, {2, 4, 8, 4, false}, {3, 4, 8, 2, false}, {4, 4, 8, 2, false},
-    {6, 4, 4, 2, true},  {8, 4, 4, 1, false}, {4, 6, 4, 2, true},  {4, 8, 4, 2, true}};
+    {6, 4, 4, 2, true},  {8, 4, 4, 1, false}, {4, 6, 4, 2, true}};
 
 static constexpr int most_row_tiles() {
   int most = 0;
@@ -1018,7 +1018,6 @@ hipError_t launch_rows_any(RowsArgs a, const RowsPlan& p, const Epilogue& e, hip
   PDA_ROWS(4, 4, 8, 2, 2, false, true)
   PDA_ROWS(6, 4, 4, 2, 2, true, true)
   PDA_ROWS(4, 6, 4, 2, 2, true, true)
-  PDA_ROWS(4, 8, 4, 2, 2, true, true)
   PDA_ROWS(8, 4, 4, 1, 1, false, true)
 #undef PDA_ROWS
   return hipErrorInvalidValue;
