@@ -868,17 +868,31 @@ static constexpr int most_row_tiles() {
 
 // The form, and the k splits, with the least estimated time (us).  Per round
 // of workgroups the estimate joins, as the root of the squares, a
-// workgroup's bytes at the rate a CU takes them in (70 KB/us: its loads
+// workgroup's bytes at the rate a CU takes them in (62 KB/us: its loads
 // return in order, so activations from L2 queue behind weights from memory)
-// and the round's weights at 8 TB/s, and adds 1 us per round for its ramp
-// (once for workgroups of one tile, which share a CU: 3 x 8192 -> 10240 29.8
-// us in 1280 of them, 30.7 in 214 of three row tiles);
-// the sum over the waves takes 0.015 us per KB of accumulators, an epilogue
-// in a kernel of its own 1.5 us and 1 us per MB of partials it reads.
-// Launch costs, the same for all, are left out.  Over 143 shapes (six
-// preludes and five output projections at 13 batches from 1 to 256; 2329
-// timed forms) the form chosen is on average 1.2% slower than the fastest
-// one, at most 8%.
+// and the round's weights at 11.2 TB/s, and adds 1 us for its ramp and 0.087
+// us a step for every eight tiles of matrix instructions, the steps past the
+// end of k that fill up a block of weights among them (at 1024 x 1024 with
+// three splits they are three quarters of 2 x 4's).  One-tile workgroups
+// share a CU: their rounds run together with one ramp, their weights at 78
+// KB/us.  A round is what the CUs hold, and where column groups share an XCD
+// what the XCD with the most row groups holds (27 row groups x 3 x 3 splits
+// are 243 workgroups, but 36 on an XCD of 32 CUs: two rounds).  The sum over
+// the waves and the epilogue take 0.19 us per tile and wave, an epilogue in a
+// kernel of its own 4 us and 1 us per MB of partials it reads.  Launch costs,
+// the same for all, are left out.
+//
+// These constants are fitted to timed forms: nineteen preludes and
+// twenty-two output projections, weights of 96 x 128 to 16384 x 18432, at up
+// to 27 batches from 1 to 256 (13,500 forms; over the 540 shapes with 1024 to
+// 10240 wide weights the mean of three samples).  Over all 834 shapes the
+// form chosen is on average 0.8% slower than the fastest one, 3% or more on
+// 77 and at most 11%.  (With one rate for all bytes, nothing for the steps,
+// workgroups counted over the device and, fitted to one shape, grids of one
+// workgroup per CU left out: 1.7%, 164 shapes and 17%.)  What the estimate
+// does not see is the memory's address pattern: two row tiles a workgroup of
+// k = 8192 stream 8% slower than of 7936 or 8448, with 252, 255 or 256
+// workgroups alike.
 static RowsPlan search_rows(int batch, int n, int k, int num_cus, bool fusable, int max_splits) {
   const int nbt = (batch + 15) / 16;
   const int tiles = n / kTileRows;
@@ -894,30 +908,30 @@ static RowsPlan search_rows(int batch, int n, int k, int num_cus, bool fusable, 
     for (int fused = 0; fused <= 1; ++fused) {
       if (fused && (!fusable || f.rt % 2)) continue;
       for (int splits = 1; splits <= (fused ? 1 : max_splits); ++splits) {
-        const int64_t wgs = static_cast<int64_t>(rows) * cols * splits;
+        const int64_t wgs = static_cast<int64_t>(cols > 1 ? (rows + 7) / 8 * 8 : rows) * cols * splits;
         // workgroups of one row tile and one column tile: several reside on a
         // CU and their loads overlap, so rounds run together
         const bool small = f.rt == 1 && f.bt == 1;
-        if (splits > 1 && wgs > num_cus && !small) break;  // splitting only fills a round
-        // Exactly one workgroup of several row tiles per CU, up to 16
-        // sequences, measured 10% above its estimate (4 x 8192 -> 8192: 28.8
-        // us with two row tiles on 256 CUs, 26.3 with three on 171, 26.4 with
-        // two workgroups of one on each)
-        if (!fused && f.bt == 1 && f.rt > 1 && wgs == num_cus) continue;
+        // splitting only fills a round, or six of one-tile workgroups (more
+        // were the fastest by at most 2.4%, and past ten were not timed)
+        if (splits > 1 && wgs > (small ? 6 : 1) * static_cast<int64_t>(num_cus)) break;
         const double wk = 2.0 * k / splits / 1e3;  // KB per row
         const double x_rows = batch < 16 * f.bt ? batch : 16 * f.bt;
-        const double in_us = (16 * f.rt + x_rows) * wk / 70.0;
-        const double w_us = 16.0 * f.rt * wk / cols / 8e3;  // per workgroup in the round
+        const double in_us = (16.0 * f.rt / (small ? 78.0 : 62.0) + x_rows / 62.0) * wk;
+        const double w_us = 16.0 * f.rt * wk / cols / 11.2e3;  // per workgroup in the round
+        const int steps = ((k + kPairK * splits - 1) / (kPairK * splits) + f.waves - 1) / f.waves;
+        const double mul_us = (steps + f.kb - 1) / f.kb * f.kb * 0.0109 * f.rt * f.bt * f.waves;
         const int64_t full = wgs / num_cus, rest = wgs % num_cus;
-        double us = 0.015 * f.rt * f.bt * f.waves;
+        double us;
         if (small) {
           const double rounds = static_cast<double>(full + (rest ? 1 : 0)), w_all = static_cast<double>(wgs) * w_us;
-          us += std::sqrt(rounds * in_us * rounds * in_us + w_all * w_all) + 1.0;
+          us = std::sqrt(rounds * in_us * rounds * in_us + w_all * w_all) + 1.0 + rounds * mul_us;
         } else {
-          auto round_us = [&](double m) { return std::sqrt(in_us * in_us + m * w_us * m * w_us) + 1.0; };
-          us += full * round_us(num_cus) + (rest ? round_us(static_cast<double>(rest)) : 0.0);
+          auto round_us = [&](double m) { return std::sqrt(in_us * in_us + m * w_us * m * w_us) + 1.0 + mul_us; };
+          us = full * round_us(num_cus) + (rest ? round_us(static_cast<double>(rest)) : 0.0);
         }
-        if (!fused) us += 1.5 + 4e-6 * splits * batch * static_cast<double>(n);
+        us += 0.19 * f.rt * f.bt / f.waves;
+        if (!fused) us += 4.0 + 4e-6 * splits * batch * static_cast<double>(n);
         if (best.grid && us >= best_us) continue;
         best_us = us;
         best.rt = f.rt, best.bt = f.bt, best.waves = f.waves, best.kb = f.kb, best.wide = f.wide;
