@@ -47,17 +47,12 @@ def ref(w):
     return oracle.o_proj_residual_norm(w.attn, w.w_o, w.residual, w.norm_w, w.eps)
 
 
+# model-like and small sizes on both sides of the batches where the column
+# tiles change (16, 32, 64), with hidden sizes that divide by 16 only and up
+# to the limit; the forms of the kernel have tests of their own
 SMALL = [(1, 32, 16), (3, 96, 48), (17, 4096, 2560), (64, 512, 1024), (5, 64, 32768), (33, 8192, 256),
-         # one batch tile of more than 4 sequences: four row tiles share each x
-         # fragment when the row tiles divide by four (1040 rows do not)
          (8, 96, 48), (12, 2048, 1040), (16, 3072, 3072), (9, 1024, 4096),
-         # more than 16 sequences: the thin-GEMM form when the row tiles divide
-         # by 8, otherwise the per-wave form with 2, 3 or 4 row tiles per unit
-         # (1056 rows: 66 tiles; 1088: 68) or one (1040: 65)
          (32, 256, 1056), (48, 512, 1056), (64, 512, 1088), (40, 1024, 1040), (64, 4096, 4096),
-         # above 64 sequences: the thin-GEMM form with 8 or 16 column tiles;
-         # above 128 its tile-major partials go to the two-sequence epilogue,
-         # whose last workgroup has one sequence at an odd batch
          (65, 1024, 1024), (128, 512, 2048), (200, 256, 384), (256, 2048, 1280),
          (129, 512, 1024), (255, 1024, 640)]
 
@@ -113,8 +108,8 @@ def test_oproj_graph_replay(lib):
 
 
 def test_oproj_rows_not_8_byte_aligned(lib):
-    # the one-kernel epilogue (batch <= 16) moves four bf16 features at a
-    # time; rows offset by one element take the two passes, same results
+    # the kernels move up to four bf16 features at a time, at any alignment:
+    # rows offset by one element give the same bits
     import torch
     w = W.build_oproj(5, 1024, 2048, seed=11)
     attn, nw = dev_bf16(w.attn), dev_bf16(w.norm_w)
