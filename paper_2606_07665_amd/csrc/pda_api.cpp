@@ -378,10 +378,11 @@ Plan make_split_plan(int32_t batch, int32_t hkv, int32_t d, int64_t steps_seq, i
 // takes about 6 us + its K/V bytes at 42 KB/us, a split plan at least 9 us
 // (its merge kernel and boundary are 4 of them), and 13 where the pairs are
 // too many for the fixed split, since its workgroups then take several
-// sequences one after another.  Replayed from a graph, split -> whole: 16 x
-// 160 tokens, 32:8 heads 10.2 -> 7.9 us; 64 x 64 10.7 -> 7.7; 256 x 64 18.6
-// -> 12.3; 32:2 heads, 128 x 64 27.5 -> 7.6, 256 x 256 40 -> 14.  With longer
-// sequences a few long ones among short ones would cost more whole.
+// sequences one after another.  Replayed from a graph over cold K/V, split ->
+// whole: 16 x 160 tokens, 32:8 heads 10.5 -> 8.2 us; 64 x 64 10.9 -> 8.5; 256
+// x 64 19.9 -> 14.7; 32:2 heads, 128 x 64 17.9 -> 7.8, 256 x 256 22.3 ->
+// 15.9.  With longer sequences a few long ones among short ones would cost
+// more whole.
 Plan plan_whole(const Plan& split, int32_t batch, int32_t hkv, int32_t d, int64_t steps_seq, int num_cus) {
   Plan pl = split;
   pl.grid = 0;

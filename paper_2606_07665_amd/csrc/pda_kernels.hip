@@ -375,14 +375,16 @@ __global__ __launch_bounds__(64 * max_waves(D), 1) void attn_kernel(
   // taking up another piece (page ids, then K, then V, then the exchange of
   // the phases: ~5 us that nothing overlaps).  Counted by steps alone, a
   // workgroup of a ragged batch got 8 or more short sequences in a row and
-  // the others waited for it.  A step of eight heads (one phase, D = 128) is
-  // 128 KB, ~5 us of a CU's share of memory by itself, and covers it: none
-  // there.  Batches of 31 to 256 sequences (Zipf and two-length mixes, 20 to
-  // 1000 MB), geometric mean of the time against steps alone: 8:1 heads,
-  // D = 128 0.67, 32:2 0.78, 24:4 0.89, 8:1 at D = 64 0.74, 12:4 at D = 256
-  // 0.95 (one phase), 8:1 at D = 256 0.76; with it 32:8 at D = 128 would be
-  // 1.01 and 40:40 1.04.  Half as much gives 0.76, 0.84, 0.89, 0.82, 0.98,
-  // 0.83; limits of 4 and 16 steps per phase are within 1%.
+  // the others waited for it.  With one phase a step of eight heads is 64 KB
+  // (D = 64) or 128 KB, 2.5 or 5 us of a CU's share of memory by itself, which
+  // leaves nothing to gain: none there, but for D = 256 (one wave per SIMD,
+  // four heads), where it still gives 5%.  Batches of 31 to 256
+  // sequences (Zipf and two-length mixes, 6 to 2200 MB), geometric mean of the
+  // time against steps alone: 8:1 heads, D = 128 0.53, 32:2 0.69, 24:4 0.86;
+  // D = 64 8:1 0.57, 32:2 0.69, 24:4 0.81; D = 256 8:1 0.67, 12:4 (one phase)
+  // 0.95.  With one phase at D = 64 and 128 it would be 0.99 (32:8) to 1.01
+  // (40:40, up to 1.04).  Half as much gives 0.62, 0.77, 0.87; 0.65, 0.77,
+  // 0.86; 0.74, 0.95; limits of 4 and 16 steps per phase are within 1%.
   const int extra = (phases > 1 || D == 256) ? phases : 0;
   auto extent = [&](int steps) { return steps + (steps > 0 && steps < 8 * phases ? extra : 0); };
 
