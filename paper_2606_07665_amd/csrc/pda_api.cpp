@@ -451,26 +451,54 @@ struct Workspace {
   void* ptr = nullptr;
   int64_t bytes = 0;
   int32_t* cnt = nullptr;  // arrival counters of the fused merge, zero between calls
+  std::vector<void*> outgrown;  // smaller buffers that captured graphs may hold
 };
 std::mutex g_ws_mu;
 std::map<std::pair<int, hipStream_t>, Workspace> g_ws;
 
-// needed: false where this call does without it (it then grows for later
-// calls, and not while the stream is being captured).
-int workspace_for(int dev, hipStream_t st, int64_t need, void** out, bool needed = true) {
+// A buffer of at least `least` bytes, which this call writes.  One that has to
+// grow takes `most` bytes (and a quarter), what every call that `most` covers
+// writes; one that holds `least` alone grows to that as well, so that those
+// calls can be captured later, but early: not while the stream is being
+// captured, not where it cannot, and keeping the old buffer, which a graph
+// captured before may write to, until pda_release_workspaces.  (Each buffer is
+// at least 5/4 of the one before: four times the last one are kept at most.)
+int workspace_for(int dev, hipStream_t st, int64_t least, int64_t most, void** out) {
   std::lock_guard<std::mutex> lock(g_ws_mu);
   Workspace& ws = g_ws[{dev, st}];
-  if (ws.bytes >= need) {
-    *out = ws.ptr;
-    return PDA_OK;
-  }
+  *out = ws.ptr;
+  if (ws.bytes >= most) return PDA_OK;
+  const bool fits = ws.bytes >= least;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   hipError_t e = hipStreamIsCapturing(st, &cap);
+  if (fits && (e != hipSuccess || cap != hipStreamCaptureStatusNone)) {
+    if (e != hipSuccess) (void)hipGetLastError();
+    return PDA_OK;
+  }
   if (e != hipSuccess) return hip_fail(e, "hipStreamIsCapturing");
-  if (cap != hipStreamCaptureStatusNone && !needed) return PDA_OK;
   if (cap != hipStreamCaptureStatusNone)
     return fail(PDA_ERR_HIP, "workspace must grow to %lld bytes while the stream is being captured; "
-                "call pda_workspace_reserve before capture", static_cast<long long>(need));
+                "call pda_workspace_reserve before capture", static_cast<long long>(most));
+  const int64_t grow = most + most / 4;
+  if (fits) {
+    // another thread's capture must not see this allocation
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+      (void)hipGetLastError();
+      return PDA_OK;
+    }
+    void* p = nullptr;
+    e = hipMalloc(&p, static_cast<size_t>(grow));
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return PDA_OK;
+    }
+    if (ws.ptr) ws.outgrown.push_back(ws.ptr);
+    *out = ws.ptr = p;
+    ws.bytes = grow;
+    return PDA_OK;
+  }
   if (ws.ptr) {
     e = hipStreamSynchronize(st);  // in-flight calls may still use the old buffer
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
@@ -478,7 +506,6 @@ int workspace_for(int dev, hipStream_t st, int64_t need, void** out, bool needed
     ws.ptr = nullptr;
     ws.bytes = 0;
   }
-  const int64_t grow = need + need / 4;
   if ((e = hipMalloc(&ws.ptr, static_cast<size_t>(grow))) != hipSuccess) {
     ws.ptr = nullptr;
     return hip_fail(e, "hipMalloc(workspace)");
@@ -733,9 +760,13 @@ int64_t oproj_ss_offset(const pda::RowsPlan& plan, int batch, int hidden) {
   return align256(static_cast<int64_t>(plan.splits) * batch * hidden * 4);
 }
 
+int64_t oproj_ss_bytes(int batch, int hidden, int parts) {
+  return align256(static_cast<int64_t>(batch) * (hidden / pda::kTileRows) * parts * 4);
+}
+
 int64_t oproj_ws_bytes(int batch, int hidden, int cus) {
   return align256(pda::rows_most_floats(batch, hidden, cus, oproj_splits(hidden)) * 4) +
-         align256(static_cast<int64_t>(batch) * (hidden / pda::kTileRows) * pda::kMaxSsParts * 4);
+         oproj_ss_bytes(batch, hidden, pda::kMaxSsParts);
 }
 
 bool oproj_in_range(int32_t batch, int32_t in_features, int32_t hidden) {
@@ -819,7 +850,8 @@ int run_prelude(const void* x, const void* w_packed, const void* bias, const voi
   const pda::RowsPlan plan = pda::plan_rows(g.batch, g.n, g.k, cus, fusable, pda::kMaxRowsSplits);
   const bool fused = plan.fused;
   void* ws = nullptr;
-  if ((rc = workspace_for(dev, st, prelude_ws_bytes(d, cus), &ws, !fused))) return rc;
+  const int64_t least = fused ? 0 : align256(static_cast<int64_t>(plan.splits) * g.batch * g.n * 4);
+  if ((rc = workspace_for(dev, st, least, prelude_ws_bytes(d, cus), &ws))) return rc;
   if (!fused) {
     g.y = static_cast<float*>(ws);
     ep.y = g.y;
@@ -897,8 +929,8 @@ int attention_call(const void* q, const void* k_cache, const void* v_cache, cons
     if ((e = pda::noalloc_scratch(dev, &ws)) != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
     cnt = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + PDA_NOALLOC_SCRATCH_BYTES - counter_bytes);
   } else {
-    const int64_t need = workspace_bytes(batch, num_kv_heads, head_dim, page_size, max_pages_per_seq, cus, cols);
-    if ((rc = workspace_for(dev, st, need, &ws))) return rc;
+    const int64_t most = workspace_bytes(batch, num_kv_heads, head_dim, page_size, max_pages_per_seq, cus, cols);
+    if ((rc = workspace_for(dev, st, pl.bytes, most, &ws))) return rc;
     if (pl.fused && (rc = counters_for(dev, st, &cnt))) return rc;
   }
 
@@ -994,7 +1026,7 @@ int pda_workspace_reserve(int32_t batch, int32_t num_q_heads, int32_t num_kv_hea
   void* ptr = nullptr;
   const int64_t need =
       workspace_bytes(batch, num_kv_heads, head_dim, page_size, max_pages_per_seq, cus, pda::kMaxCols);
-  if ((rc = workspace_for(dev, static_cast<hipStream_t>(stream), need, &ptr))) return rc;
+  if ((rc = workspace_for(dev, static_cast<hipStream_t>(stream), need, need, &ptr))) return rc;
   int32_t* cnt = nullptr;
   return counters_for(dev, static_cast<hipStream_t>(stream), &cnt);
 }
@@ -1004,12 +1036,14 @@ int pda_release_workspaces(void) {
   std::lock_guard<std::mutex> lock(g_ws_mu);
   int rc = PDA_OK;
   for (auto& kv : g_ws) {
-    if (!kv.second.ptr && !kv.second.cnt) continue;
+    if (!kv.second.ptr && !kv.second.cnt) continue;  // (outgrown buffers have a successor in ptr)
     int cur = 0;
     hipError_t e = hipGetDevice(&cur);
     if (e == hipSuccess) e = hipSetDevice(kv.first.first);
     if (e == hipSuccess) e = hipStreamSynchronize(kv.first.second);
     if (e == hipSuccess && kv.second.ptr) e = hipFree(kv.second.ptr);
+    for (void* p : kv.second.outgrown)
+      if (e == hipSuccess) e = hipFree(p);
     if (e == hipSuccess && kv.second.cnt) e = hipFree(kv.second.cnt);
     const hipError_t back = hipSetDevice(cur);
     if (e == hipSuccess) e = back;
@@ -1342,7 +1376,8 @@ int pda_o_proj_residual_norm(const void* attn, const void* w_packed, const void*
   hipStream_t st = static_cast<hipStream_t>(stream);
   const pda::RowsPlan plan = oproj_plan(batch, in_features, hidden, cus);
   void* ws = nullptr;
-  if ((rc = workspace_for(dev, st, oproj_ws_bytes(batch, hidden, cus), &ws))) return rc;
+  const int64_t least = oproj_ss_offset(plan, batch, hidden) + oproj_ss_bytes(batch, hidden, plan.ss_parts);
+  if ((rc = workspace_for(dev, st, least, oproj_ws_bytes(batch, hidden, cus), &ws))) return rc;
   pda::OProjArgs o;
   o.residual = static_cast<const uint16_t*>(residual);
   o.norm_w = static_cast<const uint16_t*>(norm_w);
@@ -1388,7 +1423,8 @@ int pda_o_proj_workspace_reserve(int32_t batch, int32_t in_features, int32_t hid
   int rc = device_cus(dev, &cus);
   if (rc) return rc;
   void* ptr = nullptr;
-  return workspace_for(dev, static_cast<hipStream_t>(stream), oproj_ws_bytes(batch, hidden, cus), &ptr);
+  const int64_t need = oproj_ws_bytes(batch, hidden, cus);
+  return workspace_for(dev, static_cast<hipStream_t>(stream), need, need, &ptr);
 }
 
 int pda_o_proj_plan(int32_t batch, int32_t in_features, int32_t hidden, int32_t num_cus, pda_projection* out) {
@@ -1448,7 +1484,8 @@ int pda_prelude_workspace_reserve(const pda_prelude_dims* dims, void* stream) {
   int cus = 0;
   if ((rc = device_cus(dev, &cus))) return rc;
   void* ptr = nullptr;
-  return workspace_for(dev, static_cast<hipStream_t>(stream), prelude_ws_bytes(*dims, cus), &ptr);
+  const int64_t need = prelude_ws_bytes(*dims, cus);
+  return workspace_for(dev, static_cast<hipStream_t>(stream), need, need, &ptr);
 }
 
 }  // extern "C"

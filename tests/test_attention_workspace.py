@@ -59,3 +59,53 @@ def test_windows_share_a_workspace(gpu_lib, b, hq, hkv, d, cap):
             torch.cuda.synchronize()
             assert torch.equal(out, want[w])
             del g
+
+
+@pytest.mark.gpu
+def test_a_buffer_that_holds_the_plan_is_captured_and_kept(gpu_lib):
+    """A single request's plan over an 8192-token table writes 534 KB, a
+    shorter table's buffer has 688 KB: the call is captured with that, and once
+    later calls have grown the stream's workspace the graph still writes to
+    its own."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(7)
+
+    def bf(*shape):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    hq, hkv, d = 32, 8, 128
+    k, v, q = bf(512, 16, hkv, d), bf(512, 16, hkv, d), bf(4, hq, d)
+    bt = torch.randperm(512, dtype=torch.int32, device="cuda", generator=gen).repeat(4, 1)
+    lens = torch.tensor([8000, 7000, 100, 5000], dtype=torch.int32, device="cuda")
+    out = torch.empty_like(q)
+
+    def attend(b, pages):
+        """The arguments of b requests over a table of `pages` pages."""
+        return q[:b], k, v, bt[:b, :pages].contiguous(), lens[:b].clamp(max=pages * 16), out[:b], d ** -0.5
+
+    one, short, more = attend(1, 512), attend(1, 64), attend(4, 512)
+    gpu_lib.paged_decode_attention(*one)
+    torch.cuda.synchronize()
+    want = out[:1].clone()
+    gpu_lib.release_workspaces()
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    gpu_lib.paged_decode_attention(*short, stream=s)
+    torch.cuda.synchronize()
+    print("capture", flush=True)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        gpu_lib.paged_decode_attention(*one, stream=s)
+    for args in (one, more):  # `one` fits, and grows the workspace early
+        gpu_lib.paged_decode_attention(*args, stream=s)
+        torch.cuda.synchronize()
+        others = [torch.full((1 << 19,), 7, dtype=torch.int32, device="cuda") for _ in range(32)]
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[:1], want)
+        assert all(bool((t == 7).all()) for t in others)
+        del others
+        torch.cuda.empty_cache()
+    del g
+    gpu_lib.release_workspaces()

@@ -126,3 +126,64 @@ def test_a_workspace_of_one_batch_serves_smaller_captures(gpu_lib, warm):
         first[0].replay()
         for a, b in zip(results(), want):
             assert torch.equal(a, b)
+
+
+@pytest.mark.gpu
+def test_a_buffer_that_holds_the_plan_is_captured_and_kept(gpu_lib):
+    """One sequence's buffer of o_proj has 87 KB, the plan of four writes 74
+    KB: captured with that, whatever a buffer for all smaller batches has; a
+    fused prelude is captured with none; and later calls leave the graph the
+    buffer that it writes to."""
+    import torch
+    lib = gpu_lib
+    k = h = 4096
+    small, b = o_proj_bytes(1), 4
+    assert o_proj_bytes(b, plan=True) <= small * 5 // 4 < o_proj_bytes(b)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+
+    def bf(*shape):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    wo, w = lib.pack_weights(bf(h, k) * 0.02), lib.pack_weights(bf(6144, h) * 0.02)
+    x, res, nw = bf(16, k), bf(16, h), bf(h)
+    z, hn, q = torch.empty_like(res), torch.empty_like(res), bf(16, 32, 128)
+    kv = torch.empty((2, 16, 8, 128), dtype=torch.bfloat16, device="cuda")
+    lens = torch.arange(1, 17, dtype=torch.int32, device="cuda")
+
+    def calls(n, stream=None):
+        lib.o_proj_residual_norm(x[:n], wo, res[:n], nw, z[:n], hn[:n], stream=stream)
+        lib.attention_prelude(x[:n], w, lens[:n], q[:n], kv[0, :n], kv[1, :n], num_q_heads=32, num_kv_heads=8, head_dim=128,
+                              rope_theta=1e4, stream=stream)
+    assert lib.prelude_plan(lib.prelude_dims(b, h, 32, 8, 128, 128, 0, 1e4, 1e-6)).fused
+    calls(b)
+    torch.cuda.synchronize()
+    want = [t.clone() for t in (z[:b], hn[:b], q[:b], kv[:, :b])]
+    lib.release_workspaces()
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    lib.o_proj_residual_norm(x[:1], wo, res[:1], nw, z[:1], hn[:1], stream=s)
+    torch.cuda.synchronize()
+    print("capture", flush=True)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        calls(b, s)
+    for n in (b, 1, 16):
+        calls(n, s)
+        torch.cuda.synchronize()
+        others = [torch.full((1 << 19,), 7, dtype=torch.int32, device="cuda") for _ in range(32)]
+        for t in (z, hn, q, kv):
+            t.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for got, t in zip((z[:b], hn[:b], q[:b], kv[:, :b]), want):
+            assert torch.equal(got, t)
+        assert all(bool((t == 7).all()) for t in others)
+        del others
+        torch.cuda.empty_cache()
+    del g
+    lib.release_workspaces()
+
+
+def o_proj_bytes(batch, plan=False):
+    p, need = oproj(batch, 4096, 4096, 256)
+    return need if plan else p.workspace_bytes
