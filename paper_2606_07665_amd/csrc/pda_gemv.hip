@@ -884,15 +884,22 @@ static constexpr int most_row_tiles() {
 //
 // These constants are fitted to timed forms: nineteen preludes and
 // twenty-two output projections, weights of 96 x 128 to 16384 x 18432, at up
-// to 27 batches from 1 to 256 (13,500 forms; over the 540 shapes with 1024 to
-// 10240 wide weights the mean of three samples).  Over all 834 shapes the
-// form chosen is on average 0.8% slower than the fastest one, 3% or more on
-// 77 and at most 11%.  (With one rate for all bytes, nothing for the steps,
-// workgroups counted over the device and, fitted to one shape, grids of one
-// workgroup per CU left out: 1.7%, 164 shapes and 17%.)  What the estimate
-// does not see is the memory's address pattern: two row tiles a workgroup of
-// k = 8192 stream 8% slower than of 7936 or 8448, with 252, 255 or 256
-// workgroups alike.
+// to 27 batches from 1 to 256 (13,500 forms of 834 shapes).
+//
+// Two rules hold where a workgroup has one column tile (up to 16 sequences):
+//  * Row tiles a multiple of 128 KB apart (k a multiple of 4096) take 8% longer
+//    where a workgroup reads several of them and nearly every CU has one
+//    workgroup: two row tiles at 8 x 8192 -> 8192 (256 workgroups) 26.5 to 30.3
+//    us by where the weights lie, 24.3 and 25.7 at k = 7936 and 8448; 3 us over
+//    them with 248 workgroups, 1.7 with 224; 0 to 4% with 160 and 192, or in
+//    several rounds (288 to 512).  With one row tile 25.2, 24.8 and 26.0.
+//  * Four row tiles are not split along k: that was the fastest form on 4 of
+//    190 shapes, and chosen by the estimate on 8 x 4096 -> 8192 (20.9 us, one
+//    row tile 15.3) and 8 x 8192 -> 8192 (29.2, 25.4).
+// Over output projections of 1 to 16 sequences, weights 2048 to 12288 wide
+// with 2560 to 10240 rows (190 shapes, up to 16 forms each), the form chosen is
+// on average 0.9% slower than the fastest and at most 8%; without the two
+// rules 2.6% and 37%.
 static RowsPlan search_rows(int batch, int n, int k, int num_cus, bool fusable, int max_splits) {
   const int nbt = (batch + 15) / 16;
   const int tiles = n / kTileRows;
@@ -915,10 +922,13 @@ static RowsPlan search_rows(int batch, int n, int k, int num_cus, bool fusable, 
         // splitting only fills a round, or six of one-tile workgroups (more
         // were the fastest by at most 2.4%, and past ten were not timed)
         if (splits > 1 && wgs > (small ? 6 : 1) * static_cast<int64_t>(num_cus)) break;
+        if (splits > 1 && f.bt == 1 && f.rt >= 4) break;
         const double wk = 2.0 * k / splits / 1e3;  // KB per row
         const double x_rows = batch < 16 * f.bt ? batch : 16 * f.bt;
-        const double in_us = (16.0 * f.rt / (small ? 78.0 : 62.0) + x_rows / 62.0) * wk;
-        const double w_us = 16.0 * f.rt * wk / cols / 11.2e3;  // per workgroup in the round
+        const bool all_cus = 8 * wgs >= 7 * static_cast<int64_t>(num_cus) && wgs <= num_cus;
+        const double apart = f.bt == 1 && f.rt > 1 && k % 4096 == 0 && all_cus ? 1.08 : 1.0;
+        const double in_us = (16.0 * f.rt / (small ? 78.0 : 62.0) + x_rows / 62.0) * wk * apart;
+        const double w_us = 16.0 * f.rt * wk / cols / 11.2e3 * apart;  // per workgroup in the round
         const int steps = ((k + kPairK * splits - 1) / (kPairK * splits) + f.waves - 1) / f.waves;
         const double mul_us = (steps + f.kb - 1) / f.kb * f.kb * 0.0109 * f.rt * f.bt * f.waves;
         const int64_t full = wgs / num_cus, rest = wgs % num_cus;

@@ -93,7 +93,7 @@ OPROJ = [
     (17, 1056, 4112, "3x2 split"),
     (33, 544, 4112, "3x4 split"),
     (16, 96, 14336, "4x1 residual"),
-    (9, 2080, 4112, "4x1 split"),
+    (9, 2080, 4112, "1x1 split"),
     (17, 96, 14336, "4x2 residual"),
     (129, 288, 6656, "4x6 wide groups residual"),
     (33, 288, 16400, "6x4 wide residual"),
@@ -160,7 +160,7 @@ PRELUDE = [
     (177, 96, 2, 1, 64, dict(qk_norm=True, bias=True), "3x4 groups plain"),
     (65, 96, 2, 1, 64, dict(qk_norm=True, interleaved=True), "3x4 groups split"),
     (16, 96, 96, 8, 128, dict(qk_norm=True, rotary_dim=64), "4x1 plain"),
-    (9, 2080, 12, 4, 256, dict(qk_norm=True, interleaved=True, bias=True, rotary_dim=128), "4x1 split"),
+    (9, 2080, 12, 4, 256, dict(qk_norm=True, interleaved=True, bias=True, rotary_dim=128), "1x1 split"),
     (17, 96, 96, 8, 128, dict(qk_norm=True), "4x2 plain"),
     (17, 2080, 12, 4, 256, dict(qk_norm=True, bias=True), "4x2 split"),
     (33, 160, 96, 8, 128, dict(qk_norm=True, interleaved=True), "4x4 plain"),

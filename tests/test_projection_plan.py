@@ -47,6 +47,20 @@ def test_no_line_at_one_workgroup_per_cu(b, k, n):
     assert len({(p.row_tiles, p.col_tiles, p.k_splits) for p in near}) == 1
 
 
+@pytest.mark.parametrize("k,n", [(8192, 8192), (4096, 8192), (12288, 8192), (8192, 7936)])
+@pytest.mark.parametrize("b", [4, 6, 8, 10])
+def test_row_tiles_128_kb_apart(b, k, n):
+    """k a multiple of 4096, rows for a round of workgroups of two row tiles,
+    or of four with two splits: one row tile a workgroup is faster."""
+    p = B.o_proj_plan(b, k, n, CUS)
+    assert (p.row_tiles, p.col_tiles, p.k_splits) == (1, 1, 1)
+
+
+def test_four_row_tiles_of_one_column_tile_are_not_split():
+    for b, k, n, p in o_proj_plans(*SIZES):
+        assert (p.row_tiles, p.col_tiles) != (4, 1) or p.k_splits == 1, (b, k, n)
+
+
 # sizes that between them reach every form and ending of the planner (k in odd
 # numbers of tiles, hidden sizes and head counts up to the limits)
 KS = [96, 160, 224, 288, 544, 800, 1056, 1312, 2080, 2592, 3104, 4128, 5152, 8224, 16416, 65504]
