@@ -311,6 +311,8 @@ int pda_plan(int32_t batch, int32_t num_q_heads, int32_t num_kv_heads, int32_t h
  * with: reserve the largest shape before capturing, and neither grow that
  * stream's workspace (a larger eager call on the same stream) nor release it
  * (pda_release_workspaces) while the graph may still be replayed.
+ * (A call that fits the workspace never frees it: where it takes a larger one
+ * for later calls, the old one is kept until pda_release_workspaces.)
  */
 int pda_workspace_reserve(int32_t batch, int32_t num_q_heads, int32_t num_kv_heads,
                           int32_t head_dim, int32_t page_size, int32_t max_pages_per_seq,

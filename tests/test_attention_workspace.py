@@ -109,3 +109,43 @@ def test_a_buffer_that_holds_the_plan_is_captured_and_kept(gpu_lib):
         torch.cuda.empty_cache()
     del g
     gpu_lib.release_workspaces()
+
+
+@pytest.mark.gpu
+def test_growing_early_beside_a_capture(gpu_lib):
+    """While one stream is captured, a call on another whose buffer holds its
+    plan, and could be larger, runs and leaves the capture as it is."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(8)
+
+    def bf(*shape):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    hq, hkv, d = 32, 8, 128
+    k, v, q = bf(512, 16, hkv, d), bf(512, 16, hkv, d), bf(1, hq, d)
+    bt = torch.randperm(512, dtype=torch.int32, device="cuda", generator=gen)[None].contiguous()
+    lens, few = (torch.tensor([n], dtype=torch.int32, device="cuda") for n in (8000, 1000))
+    short = bt[:, :64].contiguous()
+    outs = [torch.empty_like(q) for _ in range(2)]
+    gpu_lib.paged_decode_attention(q, k, v, bt, lens, outs[0], d ** -0.5)
+    torch.cuda.synchronize()
+    want = outs[0].clone()
+    gpu_lib.release_workspaces()
+    captured, beside = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for s in (captured, beside):
+        gpu_lib.paged_decode_attention(q, k, v, short, few, outs[0], d ** -0.5, stream=s)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    print("capture", flush=True)
+    with torch.cuda.graph(g, stream=captured):
+        gpu_lib.paged_decode_attention(q, k, v, bt, lens, outs[0], d ** -0.5, stream=captured)
+        gpu_lib.paged_decode_attention(q, k, v, bt, lens, outs[1], d ** -0.5, stream=beside)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[1], want)
+    outs[0].zero_()
+    torch.cuda.synchronize()
+    g.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], want)
+    del g
+    gpu_lib.release_workspaces()
